@@ -84,7 +84,6 @@ constexpr int kThreads = 64 * kWaves;
 constexpr int kCThreads = 64 * kConsumers;
 constexpr int kStages = 2;                    // LDS stages: one per producer pair
 constexpr int kHalf = 32768;                  // K bytes (and V bytes) of one tile
-constexpr int kMaxDma = 18;                   // DMA instructions per producer wave and K (or V) tile, at most
 constexpr int kBlk = 16;                      // keys (and query rows) per MFMA block
 constexpr int kMaxRows = 128;                 // row blocks per unit <= 8
 constexpr int kDefaultGrid = 256;             // persistent workgroups: one per CU of an MI355X
@@ -140,6 +139,7 @@ struct Params {
   int Rcap;         // C_max * g
   int P;            // persistent workgroups
   float sl2;        // scale * log2(e)
+  int flat;         // the schedule counts tiles, not their costs (totals past 32 bits)
   const uint64_t* draft_mask;   // [B][C_max] draft-mask words (tree drafts only)
   // paged caches only: k and v are [num_pages][Hkv][1 << page_shift][D]
   const int32_t* block_table;   // [B][pages_per_seq]
@@ -165,12 +165,12 @@ struct Cfg {
   static constexpr int kLdsK = kTileKeys * kPitchK;         // LDS bytes of a staged K (V) tile
   static constexpr int kLdsV = kTileKeys * kPitchV;
   static constexpr int kStage = kLdsK + kLdsV;
-  static constexpr int kInstK = (kTileKeys * kSlotsK + 63) / 64;   // 64-slot DMA instructions per K (V) tile
-  static constexpr int kInstV = (kTileKeys * kSlotsV + 63) / 64;
+  static constexpr int kInstK = kTileKeys * kSlotsK / 64;   // 64-slot DMA instructions per K (V) tile
+  static constexpr int kInstV = kTileKeys * kSlotsV / 64;
   static constexpr int kNKB = kTileKeys / kBlk;             // 16-key blocks per tile
   static constexpr int kDB = D / 16;                        // 16-wide d blocks of O^T
   static constexpr int kQJ = kChunks / 4;                   // 16-byte Q chunks per lane
-  static_assert(kInstK <= 2 * kMaxDma && kInstV <= 2 * kMaxDma, "DMA instructions per producer wave");
+  static_assert(kTileKeys % 64 == 0, "whole 64-slot DMA instructions");
   // LDS beside the stages: packed lengths and tile prefix sums of up to
   // kMaxSeqs sequences, the key-split merge statistics and the hand-off words
   static constexpr int kLdsFixed = kMaxSeqs * 4 + (kMaxSeqs + 1) * 4 + kConsumers * 2 * kBlk * 4 + 512;
@@ -185,6 +185,16 @@ struct Cfg {
   static_assert(kMergeRegions * 64 * D <= kLdsK, "key-split merge scratch stays in the K half of a stage");
   static_assert(kNKB >= 2, "key blocks are processed in pairs");
 };
+
+// sl / SLOTS for the LDS slot sl < 4096 of a stage half, in a full-rate 24-bit
+// multiplication: M = 2^16 / SLOTS rounded up is off by less than SLOTS /
+// 2^16 per unit, which stays below 1 / SLOTS while sl (M SLOTS - 2^16) < 2^16.
+template <int SLOTS>
+__device__ __forceinline__ int slot_row(int sl) {
+  constexpr int M = (65536 + SLOTS - 1) / SLOTS;
+  static_assert(4095 * (M * SLOTS - 65536) < 65536, "exact for every slot");
+  return (int)((((uint32_t)sl & 0xfffu) * M) >> 16);
+}
 
 // Hand-offs between the waves of a workgroup go through LDS counters that
 // only grow: a wave adds one when it has done its part, and a waiting wave
@@ -311,7 +321,9 @@ __device__ __forceinline__ int seq_tiles(uint32_t s) {
 // The weights follow measured tile times (ragged chunks, 1-7 row blocks:
 // 2.7, 3.1 and 3.3 us per tile for 1-2, 3-4 and 5-7 blocks).
 constexpr int kTileCost = 10;
-__device__ __forceinline__ int tile_cost(uint32_t s, int g) { return kTileCost + (seq_c(s) * g + kBlk - 1) / kBlk; }
+__device__ __forceinline__ int tile_cost(const Params& p, uint32_t s) {
+  return p.flat ? 1 : kTileCost + (seq_c(s) * p.g + kBlk - 1) / kBlk;
+}
 // Extra costs of a unit: at its start (a first tile that is mostly partial,
 // the switch of Q) and at its end (the result's stores and, for units of one
 // or two row blocks, the merge of the key-split states; charged after its
@@ -322,24 +334,17 @@ __device__ __forceinline__ int tile_cost(uint32_t s, int g) { return kTileCost +
 constexpr int kStartSplit = 3, kEndSplit = 9;   // units of one or two row blocks
 constexpr int kStartRest = 6, kEndRest = 0;     // larger units
 constexpr int kExtraMax = kStartSplit + kEndSplit > kStartRest + kEndRest ? kStartSplit + kEndSplit : kStartRest + kEndRest;
-__device__ __forceinline__ bool split_unit(uint32_t s, int g) { return seq_c(s) * g <= 2 * kBlk; }
-__device__ __forceinline__ int start_cost(uint32_t s, int g) { return split_unit(s, g) ? kStartSplit : kStartRest; }
-__device__ __forceinline__ int end_cost(uint32_t s, int g) { return split_unit(s, g) ? kEndSplit : kEndRest; }
-// cost of one unit (one KV head) of a sequence with packed lengths s: its n
-// tiles of cost w, its start and its end
-__device__ __forceinline__ int unit_cost(int n, int w, uint32_t s, int g) {
-  return n > 0 ? n * w + start_cost(s, g) + end_cost(s, g) : 0;
+__device__ __forceinline__ bool split_unit(const Params& p, uint32_t s) { return seq_c(s) * p.g <= 2 * kBlk; }
+__device__ __forceinline__ int start_cost(const Params& p, uint32_t s) {
+  return p.flat ? 0 : split_unit(p, s) ? kStartSplit : kStartRest;
 }
-
-// floor(a / b) for 0 <= a < 2^53 and 0 < b < 2^53: the rounded double
-// quotient is within one of it, and one exact integer step corrects it
-// (much shorter code than a 64-bit integer division).
-__device__ __forceinline__ long long div_floor(long long a, long long b) {
-  long long q = (long long)((double)a / (double)b);
-  const long long r = a - q * b;
-  if (r < 0) --q;
-  else if (r >= b) ++q;
-  return q;
+__device__ __forceinline__ int end_cost(const Params& p, uint32_t s) {
+  return p.flat ? 0 : split_unit(p, s) ? kEndSplit : kEndRest;
+}
+// cost of one unit (one KV head) of a sequence with packed lengths s: its n
+// tiles, its start and its end
+__device__ __forceinline__ int unit_cost(const Params& p, int n, uint32_t s) {
+  return n > 0 ? n * tile_cost(p, s) + start_cost(p, s) + end_cost(p, s) : 0;
 }
 
 // Tile schedule shared by every workgroup of a launch.  The tiles of all
@@ -347,55 +352,27 @@ __device__ __forceinline__ long long div_floor(long long a, long long b) {
 // unit kvh of sequence b starts at cost Hkv cpref[b] + kvh U_b + (j > 0 ?
 // S_b + j w_b : 0), w_b its sequence's tile cost, S_b and E_b its unit-start
 // and unit-end costs and U_b = n_b w_b + S_b + E_b a unit's cost, out of Wt
-// in all.  Range q holds the tiles whose start cost lies in [q Wt / Pe, (q +
-// 1) Wt / Pe).  With Pe <= Wt / max_b (w_b + S_b + E_b) no range is empty,
-// since consecutive tile starts are at most max_b (w_b + S_b + E_b) apart.
+// in all.  The costs [0, Wt) are cut into Pe ranges, the first Wt mod Pe of
+// them one longer than the rest (width); range q holds the tiles whose start
+// cost lies in it.  With Pe <= Wt / max_b (w_b + S_b + E_b) no range is
+// empty, since consecutive tile starts are at most max_b (w_b + S_b + E_b)
+// apart.  Everything fits 32 bits: a launch whose total cost could reach 2^31
+// counts tiles instead (Params::flat), fewer than 2^30 (host check).  The
+// search sits ahead of every workgroup's first load, and the list of shared
+// units ahead of its first tile's compute: with 64-bit costs and
+// double-precision quotients the first took 1.5 us and a call on two
+// sequences began to compute 6.0 us into the launch; in 32 bits 0.8 us and
+// 4.0 us (B = 4, 24 MB of K and V: 19.3 -> 17.5 us per call; B = 64, 347 MB:
+// 63.8 -> 63.2 us, as the stream makes up for most of it).
 struct Sched {
-  int N, Pe, B, Hkv, g;
-  bool uni;                 // every tile costs the same and S = 0: the same ranges, found without a search
-  long long Wt;
-  const uint32_t* seqs;     // packed lengths per sequence
-  const int* pref;          // tiles per KV head of the sequences before b
-  const int* cpref;         // cost of the units of one KV head of the sequences before b
-  // range of tile j of unit kvh of sequence b (n tiles per unit)
-  __device__ int owner(int b, int kvh, int j, int n) const {
-    if (uni) return (int)div_floor((long long)(Hkv * pref[b] + kvh * n + j) * Pe, N);
-    const int w = tile_cost(seqs[b], g);
-    const long long c =
-        (long long)Hkv * cpref[b] + (long long)kvh * unit_cost(n, w, seqs[b], g) + (j > 0 ? start_cost(seqs[b], g) + j * w : 0);
-    return (int)div_floor(c * Pe, Wt);
-  }
-  // first tile of range q (N for q = Pe); every lane of the wave takes part
-  __device__ int range_begin(int q) const {
-    if (q >= Pe) return N;
-    if (uni) return (int)div_floor((long long)q * N + Pe - 1, Pe);
-    const long long X = (long long)q * Wt;
-    // the last sequence b with Hkv cpref[b] Pe <= X: a 64-ary search of the
-    // B + 1 prefix entries; that sequence has tiles, as Hkv cpref[b + 1] Pe > X
-    const int lane = threadIdx.x & 63;
-    const int step = (B + 64) / 64;
-    const int i1 = min(lane * step, B);
-    const long long hp = (long long)Hkv * Pe;
-    const unsigned long long m1 = __ballot(cpref[i1] * hp <= X);
-    const int base = (63 - __builtin_clzll(m1)) * step;
-    const int i2 = min(base + lane, B);
-    const unsigned long long m2 = __ballot(lane < step && cpref[i2] * hp <= X);
-    const int b = __builtin_amdgcn_readfirstlane(base + 63 - __builtin_clzll(m2));
-    const int n = pref[b + 1] - pref[b];   // tiles per unit of sequence b
-    const int w = tile_cost(seqs[b], g);
-    // the unit of sequence b whose cost interval holds X, then the first of
-    // its tiles that starts at or after X (or the next unit's first tile)
-    const long long rem = X - cpref[b] * hp;   // >= 0
-    const long long U = (long long)unit_cost(n, w, seqs[b], g) * Pe;
-    const int kvh = (int)div_floor(rem, U);
-    const long long rem2 = rem - kvh * U;
-    int j = 0;
-    if (rem2 > 0) {
-      const long long den = (long long)w * Pe;
-      j = (int)div_floor(rem2 - (long long)start_cost(seqs[b], g) * Pe + den - 1, den);
-      j = j < 1 ? 1 : j > n ? n : j;   // n: the next unit's first tile
-    }
-    return Hkv * pref[b] + kvh * n + j;
+  int N, Pe;
+  uint32_t Wt, width, longer;
+  __device__ uint32_t bound(int q) const { return (uint32_t)q * width + min((uint32_t)q, longer); }   // range q's first cost
+  // range of the tile that starts at cost c
+  __device__ int owner(uint32_t c) const {
+    const uint32_t cut = longer * (width + 1);
+    const bool low = c < cut;
+    return (int)((low ? c : c - cut) / (low ? width + 1 : width) + (low ? 0 : longer));
   }
 };
 
@@ -408,31 +385,28 @@ struct Cursor {
 
 // Merge every piece of up to two units: those that this workgroup merges
 // through the workspace, run by its consumer threads after its own tiles.  A
-// unit's pieces come from ranges qf..ql; range q's piece is its first
-// segment (slot 2q), except for range qf when it starts before the unit:
-// then it is qf's last segment (slot_first = 2 qf + 1).  The (row, 4 d)
-// items of both units form one list, and each thread takes three items per
-// round and issues all their loads before it waits, so the two units' loads
-// go out together.  Unit u is described by e_u = {unit, qf, ql, slot_first}.
+// unit's pieces come from ranges qf..ql: slot 2 qf + 1 holds the piece of the
+// range that the unit starts in, slot 2 q that of a later range q.  The (row,
+// 4 d) items of both units form one list, and each thread takes three items
+// per round and issues all their loads before it waits, so the two units'
+// loads go out together.  Unit u is described by e_u = {unit, qf, ql}.
 template <int D, bool NT>
-__device__ __forceinline__ void merge_units(const Params& p, const uint32_t* seqs, int ctid, const int* e_a,
-                                         const int* e_b, bool has_a, bool has_b) {
+__device__ __forceinline__ void merge_units(const Params& p, const uint32_t* seqs, int ctid, i32x4 e_a,
+                                         i32x4 e_b, bool has_a, bool has_b) {
   const __amdgpu_buffer_rsrc_t ws_o_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_o, 0, p.ws_o_bytes, kBufferFormat);
   const __amdgpu_buffer_rsrc_t ws_lse_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(p.ws_lse, 0, p.ws_lse_bytes, kBufferFormat);
   const int g = p.g;
-  int ua = 0, qfa = 0, qla = -1, sfa = 0, ub = 0, qfb = 0, qlb = -1, sfb = 0;
+  int ua = 0, qfa = 0, qla = -1, ub = 0, qfb = 0, qlb = -1;
   if (has_a) {
     ua = uniform(e_a[0]);
     qfa = uniform(e_a[1]);
     qla = uniform(e_a[2]);
-    sfa = uniform(e_a[3]);
   }
   if (has_b) {
     ub = uniform(e_b[0]);
     qfb = uniform(e_b[1]);
     qlb = uniform(e_b[2]);
-    sfb = uniform(e_b[3]);
   }
   const int n_a = has_a ? seq_c(uniform(seqs[ua / p.Hkv])) * g * (D / 4) : 0;
   const int n_b = has_b ? seq_c(uniform(seqs[ub / p.Hkv])) * g * (D / 4) : 0;
@@ -443,7 +417,7 @@ __device__ __forceinline__ void merge_units(const Params& p, const uint32_t* seq
   for (int base = ctid; base < n_items; base += kItems * kCThreads) {
     float m[kItems], z[kItems];
     f32x4 acc[kItems];
-    int srow0[kItems], qf[kItems], ql[kItems], sf[kItems], d0[kItems];
+    int srow0[kItems], qf[kItems], ql[kItems], d0[kItems];
     size_t orow[kItems];
 #pragma unroll
     for (int it = 0; it < kItems; ++it) {
@@ -458,7 +432,6 @@ __device__ __forceinline__ void merge_units(const Params& p, const uint32_t* seq
       d0[it] = 4 * (local - r * (D / 4));
       qf[it] = in_a ? qfa : qfb;
       ql[it] = idx < n_items ? (in_a ? qla : qlb) : -1;   // no pieces for a lane past the items
-      sf[it] = in_a ? sfa : sfb;
       srow0[it] = r;
       const int b = unit / p.Hkv;
       orow[it] = (size_t)(b * p.C_max + r / g) * p.Hq + (unit - b * p.Hkv) * g + r % g;
@@ -471,7 +444,7 @@ __device__ __forceinline__ void merge_units(const Params& p, const uint32_t* seq
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
           const int q = qf[it] + k0 + u;
-          const int srow = (k0 + u == 0 ? sf[it] : 2 * q) * p.Rcap + srow0[it];
+          const int srow = (k0 + u == 0 ? 2 * q + 1 : 2 * q) * p.Rcap + srow0[it];
           if (q <= ql[it]) {
             lq[it][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ws_lse_rsrc, srow * 4, 0,
                                                                                      kDeviceCoherent));
@@ -541,7 +514,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
   __shared__ float mst[kConsumers][2][kBlk];   // key-split merge: max and sum of each wave's rows
   __shared__ int sh_flag[2];              // "this piece completed its unit", for the two pieces
   __shared__ int sh_direct;               // the next range's piece of the last unit had arrived at the last tile
-  __shared__ int sh_share[2][4];          // unit, qf, ql, slot_first of the units of tiles g0 and g1 - 1
+  __shared__ __attribute__((aligned(16))) i32x4 sh_share[2];   // unit, qf, ql of the units of tiles g0 and g1 - 1
   __shared__ int full_cnt[kStages];       // producer waves whose loads of the stage's tile have landed
   __shared__ int empty_cnt[kStages];      // consumer waves done with the stage's tile
   __shared__ int cb_cnt;                  // consumer waves that reached a consumer barrier
@@ -585,79 +558,59 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     }
   };
 
-  // Cursor of global tile t: a 64-ary search of the prefix sums, done by a
-  // whole wave (two LDS reads and two ballots).
-  auto locate = [&](int t) {
-    const int tq = t / Hkv;                      // tiles per KV head before t's sequence, at most
-    const int step = (B + 64) / 64;              // B + 1 prefix entries in 64 groups
-    const int i1 = min(lane * step, B);
-    const unsigned long long m1 = __ballot(pref[i1] <= tq);
-    const int base = (63 - __builtin_clzll(m1)) * step;
-    const int i2 = min(base + lane, B);
-    const unsigned long long m2 = __ballot(lane < step && pref[i2] <= tq);
-    Cursor cu;
-    cu.b = uniform(base + 63 - __builtin_clzll(m2));
-    cu.s = uniform(seqs[cu.b]);
-    const int n = seq_tiles<C>(cu.s);
-    const int off = t - Hkv * uniform(pref[cu.b]);
-    cu.kvh = off / n;
-    cu.j = off - cu.kvh * n;
-    return cu;
-  };
-  Sched sc;
-  sc.B = B;
-  sc.Hkv = Hkv;
-  sc.g = g;
-  sc.seqs = seqs;
-  sc.pref = pref;
-  sc.cpref = cpref;
-  // every tile costs at most w_hi, so with at most Wt / w_hi ranges (and at
-  // least one when there are tiles) no range is empty
-  const int w_hi = kTileCost + (p.C_max * g + kBlk - 1) / kBlk + kExtraMax;
-  auto set_totals = [&](int tiles_per_head, int cost_per_head) {
-    sc.N = tiles_per_head * Hkv;   // tiles of all units (< 2^30, host check)
-    sc.Wt = (long long)Hkv * cost_per_head;
-    long long pe = div_floor(sc.Wt, w_hi);
-    if (pe < 1) pe = sc.N > 0 ? 1 : 0;
-    sc.Pe = pe < p.P ? (int)pe : p.P;
-    sc.uni = kExtraMax == 0 && sc.Wt == (long long)sc.N * w_hi;
-  };
-
   // ---- prologue, by wave 0 alone while the other waves wait at one
-  // barrier (every wave doing it was issue-bound): the lengths, tile and cost
-  // prefix sums into LDS, then this workgroup's range [g0, g1) and its first
-  // tile.  Lane l owns the contiguous sequences [l per, (l + 1) per).  Every
-  // range is streamed in order.
-  __shared__ int sh_sched[12];
+  // barrier (every wave doing it was issue-bound): the lengths into LDS,
+  // their tile and cost prefix sums, then this workgroup's range [g0, g1),
+  // its first tile and the units of its first and last tile.  Lane l owns the
+  // contiguous sequences [l per, (l + 1) per).  Every range is streamed in
+  // order.
+  __shared__ __attribute__((aligned(16))) i32x4 sh_sched[4];
+  Sched sc;
   if (wave == 0) {
     const int per = (B + 63) / 64;
     const int b_lo = min(lane * per, B);
     const int b_hi = min(b_lo + per, B);
     int my_tiles = 0, my_cost = 0;   // sums < 2^31 (host check)
     uint32_t my_s = 0;               // (B <= 64) the packed lengths of sequence lane
-    for (int b = b_lo; b < b_hi; ++b) {
-      const uint32_t s = load_seq(p, b);
-      seqs[b] = s;
-      my_s = s;
-      my_tiles += seq_tiles<C>(s);
-      my_cost += unit_cost(seq_tiles<C>(s), tile_cost(s, g), s, g);
+    auto add = [&](uint32_t s) {     // (s = 0: no tiles, no cost)
+      const int n = seq_tiles<C>(s);
+      my_tiles += n;
+      my_cost += unit_cost(p, n, s);
+    };
+    if (per == 1) {
+      if (lane < B) {
+        my_s = load_seq(p, lane);
+        seqs[lane] = my_s;
+      }
+      add(my_s);
+    } else {
+      // (all loads of four sequences before their first use)
+      for (int b = b_lo; b < b_hi; b += 4) {
+        uint32_t s4[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s4[u] = b + u < b_hi ? load_seq(p, b + u) : 0u;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (b + u < b_hi) seqs[b + u] = s4[u];
+          add(s4[u]);
+        }
+      }
     }
     const int incl = wave_scan(my_tiles), cincl = wave_scan(my_cost);
-    const int total = __builtin_amdgcn_readlane(incl, 63);
-    const int ctotal = __builtin_amdgcn_readlane(cincl, 63);
-    // exclusive prefixes: pref[b_lo] and cpref[b_lo] (the totals in lanes
-    // without sequences)
+    // exclusive prefixes: those of sequence b_lo (the totals in lanes without
+    // sequences)
     const int ex = incl - my_tiles, cex = cincl - my_cost;
-    int run = ex, crun = cex;
-    for (int b = b_lo; b < b_hi; ++b) {
-      pref[b] = run;
-      cpref[b] = crun;
-      run += seq_tiles<C>(seqs[b]);
-      crun += unit_cost(seq_tiles<C>(seqs[b]), tile_cost(seqs[b], g), seqs[b], g);
-    }
-    if (lane == 63) {
-      pref[B] = total;
-      cpref[B] = ctotal;
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    if (per > 1) {
+      int run = ex, crun = cex;
+      for (int b = b_lo; b < b_hi; ++b) {
+        const uint32_t s = seqs[b];
+        const int n = seq_tiles<C>(s);
+        pref[b] = run;
+        cpref[b] = crun;
+        run += n;
+        crun += unit_cost(p, n, s);
+      }
     }
     if (lane < kStages) {
       full_cnt[lane] = 0;
@@ -668,87 +621,98 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       pub_arrive[lane] = 0;
       sh_flag[lane] = 0;
     }
-    set_totals(total, ctotal);
-    // With at most 64 sequences lane l holds sequence l (one per lane), and
-    // with ex = pref[min(l, B)], cex = cpref[min(l, B)] the searches below
-    // run on registers and ballots instead of LDS round trips: the same
-    // results as Sched::range_begin and locate.
-    const bool in_regs = B <= 64;
-    auto range_begin_w0 = [&](int q) {
-      if (!in_regs || q >= sc.Pe || sc.uni) return sc.range_begin(q);
-      const long long X = (long long)q * sc.Wt, hp = (long long)Hkv * sc.Pe;
-      // lane 0 (cex = 0) always passes, lanes from B on (cex = ctotal, and
-      // ctotal hp = Pe Wt > X) never do
-      const unsigned long long m = __ballot((long long)cex * hp <= X);
-      const int b = 63 - __builtin_clzll(m);
-      const int n = __builtin_amdgcn_readlane(my_tiles, b);
-      const uint32_t s_b = (uint32_t)__builtin_amdgcn_readlane((int)my_s, b);
-      const int w = tile_cost(s_b, g);
-      const long long rem = X - (long long)__builtin_amdgcn_readlane(cex, b) * hp;
-      const long long U = (long long)unit_cost(n, w, s_b, g) * sc.Pe;
-      const int kvh = (int)div_floor(rem, U);
-      const long long rem2 = rem - kvh * U;
-      int j = 0;
-      if (rem2 > 0) {
-        const long long den = (long long)w * sc.Pe;
-        j = (int)div_floor(rem2 - (long long)start_cost(s_b, g) * sc.Pe + den - 1, den);
-        j = j < 1 ? 1 : j > n ? n : j;
+    // every tile costs at most w_hi with its unit's start and end, so with at
+    // most Wt / w_hi ranges (and at least one when there are tiles) no range
+    // is empty
+    sc.N = total * Hkv;   // tiles of all units (< 2^30, host check)
+    sc.Wt = (uint32_t)Hkv * (uint32_t)__builtin_amdgcn_readlane(cincl, 63);
+    const uint32_t w_hi = p.flat ? 1 : kTileCost + (p.C_max * g + kBlk - 1) / kBlk + kExtraMax;
+    sc.Pe = sc.Wt >= (uint32_t)p.P * w_hi ? p.P : sc.N > 0 ? max((int)(sc.Wt / w_hi), 1) : 0;
+    sc.width = sc.Wt / (uint32_t)max(sc.Pe, 1);
+    sc.longer = sc.Wt - sc.width * (uint32_t)sc.Pe;
+    // The sequence whose units hold cost X < Wt: the last one with Hkv
+    // cpref[b] <= X (it has tiles, as the next prefix is past X).
+    struct At {
+      int b, n, t0;       // sequence, tiles per unit, tiles before its units
+      uint32_t s, c0, U;  // packed lengths, cost before its units, cost of a unit
+    };
+    auto seq_at = [&](uint32_t X) {
+      At a;
+      // (lane 0's prefix 0 always passes, the totals in lanes without
+      // sequences never do)
+      const int l = 63 - __builtin_clzll(__ballot((uint32_t)cex * (uint32_t)Hkv <= X));
+      if (per == 1) {
+        a.b = l;
+        a.s = (uint32_t)__builtin_amdgcn_readlane((int)my_s, l);
+        a.t0 = __builtin_amdgcn_readlane(ex, l);
+        a.c0 = (uint32_t)__builtin_amdgcn_readlane(cex, l);
+      } else {
+        // among the (at most 16) sequences of lane l
+        const int i = l * per + lane;
+        const bool below = lane < per && i < B && (uint32_t)cpref[min(i, B - 1)] * (uint32_t)Hkv <= X;
+        a.b = l * per + 63 - __builtin_clzll(__ballot(below));
+        a.s = uniform(seqs[a.b]);
+        a.t0 = uniform(pref[a.b]);
+        a.c0 = (uint32_t)uniform(cpref[a.b]);
       }
-      return Hkv * __builtin_amdgcn_readlane(ex, b) + kvh * n + j;
+      a.n = seq_tiles<C>(a.s);
+      a.t0 *= Hkv;
+      a.c0 *= (uint32_t)Hkv;
+      a.U = (uint32_t)unit_cost(p, a.n, a.s);
+      return a;
     };
-    auto locate_w0 = [&](int t) {
-      if (!in_regs) return locate(t);
-      // lane 0 (ex = 0) always passes, lanes from B on (ex = total > t / Hkv
-      // for t < N) never do
-      const unsigned long long m = __ballot(ex <= t / Hkv);
-      const int b = 63 - __builtin_clzll(m);
-      Cursor cu;
-      cu.b = b;
-      cu.s = (uint32_t)__builtin_amdgcn_readlane((int)my_s, b);
-      const int n = seq_tiles<C>(cu.s);
-      const int off = t - Hkv * __builtin_amdgcn_readlane(ex, b);
-      cu.kvh = off / n;
-      cu.j = off - cu.kvh * n;
-      return cu;
-    };
-    int g0 = 0, g1 = 0;
-    Cursor first = {0, 0, 0, 0u};
     if (pid < sc.Pe) {
-      g0 = range_begin_w0(pid);
-      g1 = range_begin_w0(pid + 1);
-      first = locate_w0(g0);
+      // the first tile that starts at or after the range's first cost, ...
+      const uint32_t X = sc.bound(pid);
+      At f = seq_at(X);
+      uint32_t kvh = (X - f.c0) / f.U;
+      uint32_t cf = f.c0 + kvh * f.U;
+      const uint32_t w = (uint32_t)tile_cost(p, f.s), S = (uint32_t)start_cost(p, f.s), r = X - cf;
+      uint32_t j = r == 0 ? 0 : r <= S ? 1 : (r - S + w - 1) / w;
+      // (rounded up to a unit's end: the next unit's first tile)
+      int g0 = f.t0 + (int)kvh * f.n + min((int)j, f.n);
+      if ((int)j >= f.n) {
+        j = 0;
+        cf += f.U;
+        if ((int)++kvh == Hkv) {
+          kvh = 0;
+          f = seq_at(cf);
+        }
+      }
+      // ... and the last one that starts before its end
+      const uint32_t Y = sc.bound(pid + 1) - 1;
+      const At e = seq_at(Y);
+      const uint32_t kvl = (Y - e.c0) / e.U;
+      const uint32_t cl = e.c0 + kvl * e.U;
+      const uint32_t wl = (uint32_t)tile_cost(p, e.s), Sl = (uint32_t)start_cost(p, e.s), rl = Y - cl;
+      const int jl = rl < Sl + wl ? 0 : min((int)((rl - Sl) / wl), e.n - 1);
+      const int g1 = e.t0 + (int)kvl * e.n + jl + 1;
+      if (lane == 0) {
+        sh_sched[1] = i32x4{g1, f.b, (int)kvh, (int)j};
+        sh_sched[2] = i32x4{(int)f.s, (int)cf, e.b, (int)kvl};
+        sh_sched[3] = i32x4{(int)e.s, (int)cl, g0, 0};
+      }
     }
-    if (lane == 0) {
-      sh_sched[0] = total;
-      sh_sched[1] = ctotal;
-      sh_sched[9] = sc.Pe;
-      sh_sched[10] = sc.uni ? 1 : 0;
-      sh_sched[2] = g0;
-      sh_sched[3] = g1;
-      sh_sched[6] = first.b;
-      sh_sched[7] = first.kvh;
-      sh_sched[8] = first.j;
-    }
+    if (lane == 0) sh_sched[0] = i32x4{sc.Pe, (int)sc.width, (int)sc.longer, sc.N};
   }
   __syncthreads();
-  if (wave != 0) {
-    sc.N = uniform(sh_sched[0]) * Hkv;
-    sc.Wt = (long long)Hkv * uniform(sh_sched[1]);
-    sc.Pe = uniform(sh_sched[9]);
-    sc.uni = uniform(sh_sched[10]) != 0;
-  }
+  const i32x4 sw0 = sh_sched[0], sw1 = sh_sched[1], sw2 = sh_sched[2], sw3 = sh_sched[3];
+  sc.Pe = uniform(sw0[0]);
+  sc.width = (uint32_t)uniform(sw0[1]);
+  sc.longer = (uint32_t)uniform(sw0[2]);
+  sc.N = uniform(sw0[3]);
   if (pid >= sc.Pe) {
     pad_rows(tid, kThreads);
     return;
   }
-  const int g0 = uniform(sh_sched[2]);
-  const int g1 = uniform(sh_sched[3]);
+  const int g0 = uniform(sw3[2]);
+  const int g1 = uniform(sw1[0]);
   const int count = g1 - g0;
   Cursor first;
-  first.b = uniform(sh_sched[6]);
-  first.kvh = uniform(sh_sched[7]);
-  first.j = uniform(sh_sched[8]);
-  first.s = uniform(seqs[first.b]);
+  first.b = uniform(sw1[1]);
+  first.kvh = uniform(sw1[2]);
+  first.j = uniform(sw1[3]);
+  first.s = (uint32_t)uniform(sw2[0]);
   // the first tile of unit (b, kvh) after cursor cu's unit
   auto next_unit = [&](Cursor& cu) {
     cu.j = 0;
@@ -787,7 +751,6 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
   // (skipping measured slower there: 77.2 -> 79.5 us on B = 64 with 16-token
   // pages, against 68.2 -> 67.2 us with a contiguous cache).  The two waves of a producer pair
   // issue the K and V instructions of even and odd index.
-  const int pw = wave & 1;
   // (paged) the pool pages of the tile of cu, one per lane of a producer
   // wave: lane l holds the page of the tile's l-th page (at most 33 of them:
   // pages hold at least 8 tokens, tiles at most 256).  Out-of-range table
@@ -804,6 +767,12 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     }
     return r;
   };
+  constexpr int kDmaK = (C::kInstK + 1) / 2, kDmaV = (C::kInstV + 1) / 2;   // loads per producer wave and tile
+  constexpr int kDmaMax = kDmaK > kDmaV ? kDmaK : kDmaV;
+  const int pw = wave & 1;
+  // Stage of the wave's pair: the first tile goes to waves 2 and 3, as wave 0
+  // comes late from the schedule.
+  const int grp = wave < 2 ? 1 : 0;
   auto dma = [&](const Cursor& cu, int st, int pg, bool all_v) {
     const int T = seq_T(cu.s);
     const int hi = T - (seq_tiles<C>(cu.s) - 1 - cu.j) * C::kTileKeys;
@@ -815,20 +784,23 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     const char* vp = p.v + slab + (size_t)lo * C::kRowBytes;
     char* kl = smem + st * C::kStage;
     char* vl = kl + C::kLdsK;
+    // Lanes past the tile's last row re-read its last 16 bytes.  A K load
+    // whose first row is past the tile's keys is skipped: those scores are
+    // masked whatever the slots hold.
+    const uint32_t end = (uint32_t)last * C::kRowBytes + 16u * (C::kChunks - 1);
+    const int n_k = (((last + 1) * C::kSlotsK + 63) / 64);
+    const int n_v = PAGED || all_v ? C::kInstV : ((last + 1) * C::kSlotsV + 63) / 64;
 #pragma unroll
-    for (int k = 0; k < kMaxDma; ++k) {
+    for (int k = 0; k < kDmaMax; ++k) {
       const int i = pw + 2 * k;
+      const char* ksrc = kp;
+      const char* vsrc = vp;
+      // the row that LDS slot sl of each half belongs to, and its 16 bytes
+      // there (a pad slot re-reads its row's last chunk)
       const int sl = 64 * i + lane;
-      // source offset of LDS slot sl in each half (a pad slot re-reads its
-      // row's last chunk)
-      const int krow_ = sl / C::kSlotsK;
-      const uint32_t koff =
-          (uint32_t)min(krow_, last) * C::kRowBytes + 16u * min(sl - krow_ * C::kSlotsK, C::kChunks - 1);
-      const int vrow_ = sl / C::kSlotsV;
-      const uint32_t voff =
-          (uint32_t)min(vrow_, last) * C::kRowBytes + 16u * min(sl - vrow_ * C::kSlotsV, C::kChunks - 1);
-      const char* ksrc = kp + koff;
-      const char* vsrc = vp + voff;
+      const int krow = slot_row<C::kSlotsK>(sl), vrow = slot_row<C::kSlotsV>(sl);
+      const uint32_t kcol = 16u * min(sl - krow * C::kSlotsK, C::kChunks - 1);
+      const uint32_t vcol = 16u * min(sl - vrow * C::kSlotsV, C::kChunks - 1);
       if constexpr (PAGED) {
         // row j of the sequence: page table[j >> shift] of the pool, row
         // j & (page - 1) of the unit's KV head in it
@@ -836,24 +808,66 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
         const int fp = lo >> sh;
         const size_t page_bytes = ((size_t)Hkv << sh) * C::kRowBytes;
         const size_t head_bytes = ((size_t)cu.kvh << sh) * C::kRowBytes;
-        const int kj = lo + min(krow_, last), vj = lo + min(vrow_, last);
+        const int kj = lo + min(krow, last), vj = lo + min(vrow, last);
         const int kpage = __shfl(pg, (kj >> sh) - fp), vpage = __shfl(pg, (vj >> sh) - fp);
-        ksrc = p.k + (size_t)kpage * page_bytes + head_bytes + (size_t)(kj & ((1 << sh) - 1)) * C::kRowBytes +
-               16u * min(sl - krow_ * C::kSlotsK, C::kChunks - 1);
-        vsrc = p.v + (size_t)vpage * page_bytes + head_bytes + (size_t)(vj & ((1 << sh) - 1)) * C::kRowBytes +
-               16u * min(sl - vrow_ * C::kSlotsV, C::kChunks - 1);
+        ksrc = p.k + (size_t)kpage * page_bytes + head_bytes + (size_t)(kj & ((1 << sh) - 1)) * C::kRowBytes + kcol;
+        vsrc = p.v + (size_t)vpage * page_bytes + head_bytes + (size_t)(vj & ((1 << sh) - 1)) * C::kRowBytes + vcol;
+      } else {
+        ksrc += (uint32_t)min(krow,last) * C::kRowBytes + kcol;
+        vsrc += (uint32_t)min(vrow,last) * C::kRowBytes + vcol;
       }
-      // a K load whose first row is past the tile's keys is skipped: those
-      // scores are masked whatever the slots hold
-      if (i < C::kInstK && sl < C::kTileKeys * C::kSlotsK && (64 * i) / C::kSlotsK <= last)
+      if (i < C::kInstK && i < n_k)
         __builtin_amdgcn_global_load_lds(ksrc, (__attribute__((address_space(3))) void*)(kl + 1024 * i), 16, 0,
                                          kStreaming);
-      if (i < C::kInstV && sl < C::kTileKeys * C::kSlotsV && (PAGED || all_v || (64 * i) / C::kSlotsV <= last))
+      if (i < C::kInstV && i < n_v)
         __builtin_amdgcn_global_load_lds(vsrc, (__attribute__((address_space(3))) void*)(vl + 1024 * i), 16, 0,
                                          kStreaming);
     }
   };
 
+
+  if (producer) {
+    // Producer pair grp streams the tiles v = grp, grp + 2, ... of the
+    // workgroup's order into stage grp: it waits until all consumers have
+    // released the stage's previous tile, issues the loads, waits for its own
+    // loads to land and counts itself on the stage's fill counter.  The two
+    // pairs run independently, so one tile's loads are issued while the
+    // other's are still in flight; only tile 1 waits until tile 0 has landed,
+    // so that at the start, when every workgroup asks for its first tiles at
+    // once, tile 0 is not delivered interleaved with tile 1.
+    Cursor cu = first;
+    int v = grp;
+    if (grp == 1 && count > 1) advance(cu);
+    int pg = 0;   // (paged) the pages of the pair's next tile
+    if constexpr (PAGED)
+      if (v < count) pg = load_pages(cu);
+    for (; v < count; v += 2) {
+      if (v >= 2) gave_up |= !wait_count(&empty_cnt[grp], kConsumers * (v >> 1), p.spin_limit);
+      if (v == 1) gave_up |= !wait_count(&full_cnt[0], 2, p.spin_limit);
+      dma(cu, grp, pg, v < 2);
+      if constexpr (PAGED) {
+        // the next tile's table entries ride the wait for this tile's loads
+        if (v + 2 < count) {
+          advance(cu);
+          advance(cu);
+          pg = load_pages(cu);
+        }
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      signal_count(&full_cnt[grp]);
+      if constexpr (!PAGED) {
+        if (v + 2 < count) {
+          advance(cu);
+          advance(cu);
+        }
+      }
+    }
+    // the padding rows of the workgroup's sequences, by the producers once
+    // their tiles are in, while the consumers compute the last ones
+    pad_rows(tid, kProducers * 64);
+    report_give_up(gave_up);
+    return;
+  }
 
   // ---- consumer roles for the unit of cursor cu.  Rows are cut into
   // n_rb 16-row blocks; consumer wave wc takes row block rb = wc % n_rbp, and
@@ -888,9 +902,9 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     const int sh = rbp_shift(n_rb);
     n_rbp = 1 << sh;
     nks = key_slots(n_rb, sh);
-    rb = producer ? 0 : wc & (n_rbp - 1);
-    kslot = producer ? nks : wc >> sh;
-    active = !producer && rb < n_rb && kslot < nks;
+    rb = wc & (n_rbp - 1);
+    kslot = wc >> sh;
+    active = rb < n_rb && kslot < nks;
     row = rb * kBlk + lm;
     row_valid = active && row < R;
     tok = row_valid ? div_g(row) : 0;
@@ -964,71 +978,21 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
   };
 
   // The first unit's Q arrives through qn, so that qr is only ever written
-  // from registers and the score MFMAs never wait for a load.  The producers
-  // start at once: the Q loads need not go out before the first tile's.
-  if (!producer) load_q(first, qn, tm_n);
-  if (producer) {
-    // Producer pair grp streams the tiles v = grp, grp + 2, ... of the
-    // workgroup's order into stage grp: it waits until all consumers have
-    // released the stage's previous tile, issues the loads, waits for its own
-    // loads to land and counts itself on the stage's fill counter.  The two
-    // pairs run independently, so one tile's loads are issued while the
-    // other's are still in flight; only tile 1 waits until tile 0 has landed,
-    // so that at the start, when every workgroup asks for its first tiles at
-    // once, tile 0 is not delivered interleaved with tile 1.
-    const int grp = wave >> 1;
-    Cursor cu = first;
-    int v = grp;
-    if (grp == 1 && count > 1) advance(cu);
-    int pg = 0;   // (paged) the pages of the pair's next tile
-    if constexpr (PAGED)
-      if (v < count) pg = load_pages(cu);
-    for (; v < count; v += 2) {
-      if (v >= 2) gave_up |= !wait_count(&empty_cnt[grp], kConsumers * (v >> 1), p.spin_limit);
-      if (v == 1) gave_up |= !wait_count(&full_cnt[0], 2, p.spin_limit);
-      dma(cu, grp, pg, v < 2);
-      if constexpr (PAGED) {
-        // the next tile's table entries ride the wait for this tile's loads
-        if (v + 2 < count) {
-          advance(cu);
-          advance(cu);
-          pg = load_pages(cu);
-        }
-      }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      signal_count(&full_cnt[grp]);
-      if constexpr (!PAGED) {
-        if (v + 2 < count) {
-          advance(cu);
-          advance(cu);
-        }
-      }
-    }
-    // the padding rows of the workgroup's sequences, by the producers once
-    // their tiles are in, while the consumers compute the last ones
-    pad_rows(tid, kProducers * 64);
-    report_give_up(gave_up);
-    return;
-  }
+  // from registers and the score MFMAs never wait for a load.
+  load_q(first, qn, tm_n);
   // Only the units of the range's first and last tile can be shared with
   // other workgroups.  Their piece bookkeeping (the ranges qf..ql that hold
-  // their tiles, and the slot of range qf's piece) is worked out now, while
-  // the first tile streams in, rather than at the end.
+  // their tiles) is worked out now, while the first tile streams in, rather
+  // than at the end.
   if (wc == 0) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const int t = k == 0 ? g0 : g1 - 1;
-      const Cursor cu = locate(t);
-      const int n = seq_tiles<C>(cu.s);
-      const int qf = sc.owner(cu.b, cu.kvh, 0, n);
-      const int ql = sc.owner(cu.b, cu.kvh, n - 1, n);
-      const int slot_first = 2 * qf + (sc.range_begin(qf) < t - cu.j ? 1 : 0);   // whole wave: a ballot search
-      if (lane == 0) {
-        sh_share[k][0] = cu.b * Hkv + cu.kvh;
-        sh_share[k][1] = qf;
-        sh_share[k][2] = ql;
-        sh_share[k][3] = slot_first;
-      }
+      const uint32_t s = (uint32_t)uniform(k == 0 ? sw2[0] : sw3[0]);
+      const uint32_t c = (uint32_t)uniform(k == 0 ? sw2[1] : sw3[1]);   // cost at which the unit starts
+      const int n = seq_tiles<C>(s);
+      if (lane == 0)
+        sh_share[k] = i32x4{k == 0 ? first.b * Hkv + first.kvh : uniform(sw2[2]) * Hkv + uniform(sw2[3]), sc.owner(c),
+                            sc.owner(n > 1 ? c + start_cost(p, s) + (n - 1) * tile_cost(p, s) : c), 0};
     }
   }
 #pragma unroll
@@ -1439,7 +1403,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       pend_inv = fl > 0.f ? 1.f / fl : 0.f;
       pend_lse = fl > 0.f ? (fm + log2f(fl)) * kLn2 : -INFINITY;
       pend_row = whole ? (b * p.C_max + tok) * p.Hq + kvh * g + row - tok * g
-                       : (2 * pid + (seg_g == g0 ? 0 : 1)) * p.Rcap + row;
+                       : (2 * pid + (unit_first >= g0 ? 1 : 0)) * p.Rcap + row;
       if (!whole) {
         Pub q;
         q.state = 0;
@@ -1825,6 +1789,12 @@ int run(const void* q, const void* k_cache, const void* v_cache, const int32_t* 
   p.Rcap = pl.Rcap;
   p.P = pl.P;
   p.sl2 = scale * kLog2e;
+  // the most a launch's tiles can cost (every sequence S_max long); past 31
+  // bits the schedule counts tiles, of which validate_desc allows fewer than
+  // 2^30
+  const int64_t tiles = (desc->S_max + key_tile(desc->dtype, desc->D) - 1) / key_tile(desc->dtype, desc->D);
+  const int64_t unit = tiles * (kTileCost + (pl.Rcap + kBlk - 1) / kBlk) + kExtraMax;
+  p.flat = (int64_t)(desc->B < kMaxSeqs ? desc->B : kMaxSeqs) * desc->Hkv * unit >= ((int64_t)1 << 31);
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();  // clear a stale error from unrelated work
