@@ -178,11 +178,11 @@ struct Cfg {
   // then the piece of the range's first segment until the range's last tile
   static constexpr int kPieceLds = (160 * 1024 - kStages * kStage - kLdsFixed) / 16 * 16;
   static_assert(kPieceLds >= (kMaxSeqs + 1) * 4, "LDS budget");
-  static_assert(kConsumers * 64 * D <= kStage, "key-split merge scratch fits in a stage");
-  // the most (row block, key slot) regions a merge uses: one block with
-  // min(kConsumers, kNKB / 2) key slots, or two blocks with two each
-  static constexpr int kMergeRegions = kConsumers < kNKB / 2 ? kConsumers : kNKB / 2 > 4 ? kNKB / 2 : 4;
-  static_assert(kMergeRegions * 64 * D <= kLdsK, "key-split merge scratch stays in the K half of a stage");
+  // the key slots of a unit of one row block, and the scratch of their merge
+  // (whole states) and of that of two slots (half states of every wave)
+  static constexpr int kMaxSlots = kConsumers < kNKB / 2 ? kConsumers : kNKB / 2;
+  static_assert(kMaxSlots * 64 * D <= kLdsK && kConsumers * 32 * D <= kLdsK,
+                "key-split merge scratch stays in the K half of a stage");
   static_assert(kNKB >= 2, "key blocks are processed in pairs");
 };
 
@@ -1030,7 +1030,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     if (v >= count && pub0.state != 0 && pub1.state != 0 && !pend) break;
     if (pend && pend_ok && !pend_direct) {
       const int s_db = nks <= C::kDB ? C::kDB / nks : 1;
-      const int d_lo = kslot * s_db, d_hi = d_lo + s_db;   // this wave's d blocks
+      const int d_lo = kslot * s_db;   // this wave's d blocks d_lo + u, in o[u]
       if (pend_whole) {
         float* dst = p.out + (size_t)pend_row * D;
         if (kslot == 0 && lg == 0) {
@@ -1038,12 +1038,13 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
           else p.lse[pend_row] = pend_lse;
         }
 #pragma unroll
-        for (int db = 0; db < C::kDB; ++db)
-          if (db >= d_lo && db < d_hi) {
+        for (int u = 0; u < C::kDB; ++u)
+          if (u < s_db && d_lo < C::kDB) {
+            f32x4* to = reinterpret_cast<f32x4*>(dst + 16 * (d_lo + u) + 4 * lg);
             if constexpr (NT)
-              __builtin_nontemporal_store(o[db] * pend_inv, reinterpret_cast<f32x4*>(dst + 16 * db + 4 * lg));
+              __builtin_nontemporal_store(o[u] * pend_inv, to);
             else
-              *reinterpret_cast<f32x4*>(dst + 16 * db + 4 * lg) = o[db] * pend_inv;
+              *to = o[u] * pend_inv;
           }
       } else {
         // read by another workgroup, possibly on another XCD
@@ -1055,10 +1056,10 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, pend_lse), ws_lse_rsrc, pend_row * 4, 0,
                                                 kDeviceCoherent);
 #pragma unroll
-        for (int db = 0; db < C::kDB; ++db)
-          if (db >= d_lo && db < d_hi)
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, o[db] * pend_inv), ws_o_rsrc,
-                                                   (pend_row * D + 16 * db + 4 * lg) * 4, 0, kDeviceCoherent);
+        for (int u = 0; u < C::kDB; ++u)
+          if (u < s_db && d_lo < C::kDB)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, o[u] * pend_inv), ws_o_rsrc,
+                                                   (pend_row * D + 16 * (d_lo + u) + 4 * lg) * 4, 0, kDeviceCoherent);
       }
     }
     if (pend && !pend_direct) {
@@ -1324,7 +1325,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       // tile's stage is the scratch; it is released only afterwards.
       float fm = m_run, fl = row_sum(l_lane);   // this lane's row: max (log2 units) and sum
       const int s_db = nks <= C::kDB ? C::kDB / nks : 1;
-      const int d_lo = kslot * s_db, d_hi = d_lo + s_db;   // this wave's d blocks
+      const int d_lo = kslot * s_db;   // the first of this wave's d blocks
       const int unit_first = gt - j;                 // global index of the unit's tile 0
       const bool whole = seg_g == unit_first && j == n - 1;
       // The piece of the range's first segment is held in LDS and stored
@@ -1337,62 +1338,93 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       // that share the LDS are no longer read.)
       const bool hold =
           HOLD && !whole && seg_g == g0 && v + 1 < count && nks > 1 && R * (D + 2) * 4 <= C::kPieceLds;
-      if (nks > 1) {
+      // Merge of NKS key slots; the result is left in o[0 .. s_db - 1].  Of two
+      // slots each writes the half of its state that the other merges; of more
+      // each writes its whole state and reads back its slice of all of them,
+      // its own among them.  Either way all of the slice's loads go out
+      // together (reads under per-slot branches, with the own blocks picked
+      // out of the registers, waited for each one: 1.8 us from the last tile's
+      // compute to here, now 1.2 us; B = 64 with 5-token chunks 63.2 -> 62.4 us
+      // per call, paged 70.1 -> 68.3 us).
+      auto merge_slots = [&](auto nks_c) {
+        constexpr int NKS = decltype(nks_c)::value;
+        constexpr int kSlice = NKS <= C::kDB ? C::kDB / NKS : 1;   // s_db
+        constexpr int kRegion = (NKS > 2 ? 64 : 32) * D;           // bytes of a wave's scratch
         char* merge_lds = smem + st * C::kStage;
         cbar();   // every consumer is done with this tile's stage
         if (active) {
-          const int region = rb * nks + kslot;
-          f32x4* reg = reinterpret_cast<f32x4*>(merge_lds + region * (64 * D));
-          // the d blocks the other waves of the row block merge (this wave
-          // keeps its own slice in registers)
+          const int region = rb * NKS + kslot;
+          f32x4* reg = reinterpret_cast<f32x4*>(merge_lds + region * kRegion) + lane;
+          if (NKS > 2) {
 #pragma unroll
-          for (int db = 0; db < C::kDB; ++db)
-            if (db < d_lo || db >= d_hi) reg[db * 64 + lane] = o[db];
+            for (int db = 0; db < C::kDB; ++db) reg[db * 64] = o[db];
+          } else if (kslot == 0) {
+#pragma unroll
+            for (int u = 0; u < kSlice; ++u) reg[u * 64] = o[kSlice + u];
+          } else {
+#pragma unroll
+            for (int u = 0; u < kSlice; ++u) {
+              reg[u * 64] = o[u];
+              o[u] = o[kSlice + u];
+            }
+          }
           if (lg == 0) {   // the four lanes of a row hold the same values
             mst[region][0][lm] = m_run;
             mst[region][1][lm] = fl;
           }
         }
         cbar();
-        if (active) {
+        if (active && d_lo < C::kDB) {
           // the same order of operations in every wave of the row block
+          const f32x4* reg = reinterpret_cast<const f32x4*>(merge_lds + rb * NKS * kRegion) + lane;
+          float mk[NKS], lk[NKS];
+          constexpr int kRead = NKS > 2 ? NKS : 1;
+          f32x4 x[kRead][kSlice];
+#pragma unroll
+          for (int k = 0; k < NKS; ++k) {
+            mk[k] = mst[rb * NKS + k][0][lm];
+            lk[k] = mst[rb * NKS + k][1][lm];
+          }
+#pragma unroll
+          for (int k = 0; k < kRead; ++k)
+#pragma unroll
+            for (int u = 0; u < kSlice; ++u)
+              x[k][u] = NKS > 2 ? reg[(k * C::kDB + d_lo + u) * 64] : reg[((1 - kslot) * kSlice + u) * 64];
           float M = -INFINITY;
-          for (int k = 0; k < nks; ++k) M = fmaxf(M, mst[rb * nks + k][0][lm]);
+#pragma unroll
+          for (int k = 0; k < NKS; ++k) M = fmaxf(M, mk[k]);
           const float Mu = M == -INFINITY ? 0.f : M;
-          float wk[kConsumers];
-          float L = 0.f;
-#pragma unroll
-          for (int k = 0; k < kConsumers; ++k) {
-            if (k < nks) {
-              wk[k] = __builtin_amdgcn_exp2f(mst[rb * nks + k][0][lm] - Mu);
-              L += mst[rb * nks + k][1][lm] * wk[k];
-            }
-          }
           fm = M;
-          fl = L;
+          fl = 0.f;
+          float wk[NKS];
 #pragma unroll
-          for (int db = 0; db < C::kDB; ++db) {
-            if (db >= d_lo && db < d_hi) {
-              f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-              for (int k = 0; k < kConsumers; ++k) {
-                if (k < nks) {
-                  const f32x4* reg = reinterpret_cast<const f32x4*>(merge_lds + (rb * nks + k) * (64 * D));
-                  acc += (k == kslot ? o[db] : reg[db * 64 + lane]) * wk[k];
-                }
-              }
-              o[db] = acc;
-              if (hold && row_valid)
-                *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(piece_lds) + row * D + 16 * db + 4 * lg) = acc;
-            }
+          for (int k = 0; k < NKS; ++k) {
+            wk[k] = __builtin_amdgcn_exp2f(mk[k] - Mu);
+            fl += lk[k] * wk[k];
           }
-          if (hold && row_valid && kslot == 0 && lg == 0) {
-            float* ps = reinterpret_cast<float*>(piece_lds) + R * D + 2 * row;
-            ps[0] = M;
-            ps[1] = L;
+          if constexpr (NKS > 2) {
+#pragma unroll
+            for (int k = 0; k < NKS; ++k)
+#pragma unroll
+              for (int u = 0; u < kSlice; ++u) o[u] = (k == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : o[u]) + x[k][u] * wk[k];
+          } else {
+            const float own = kslot == 0 ? wk[0] : wk[1], other = kslot == 0 ? wk[1] : wk[0];
+#pragma unroll
+            for (int u = 0; u < kSlice; ++u) o[u] = o[u] * own + x[0][u] * other;
+          }
+          if (hold && row_valid) {
+            float* po = reinterpret_cast<float*>(piece_lds);
+#pragma unroll
+            for (int u = 0; u < kSlice; ++u) *reinterpret_cast<f32x4*>(po + row * D + 16 * (d_lo + u) + 4 * lg) = o[u];
+            if (kslot == 0 && lg == 0) {
+              po[R * D + 2 * row] = M;
+              po[R * D + 2 * row + 1] = fl;
+            }
           }
         }
-      }
+      };
+      if (nks == 2) merge_slots(std::integral_constant<int, 2>{});
+      else if (C::kMaxSlots > 2 && nks > 1) merge_slots(std::integral_constant<int, C::kMaxSlots>{});
       signal_count(&empty_cnt[st]);   // done with stage st (and its scratch use)
 
       // ---- this wave's slice of the result, stored at the top of the next
@@ -1460,7 +1492,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       const __amdgpu_buffer_rsrc_t ws_lse_rsrc =
           __builtin_amdgcn_make_buffer_rsrc(p.ws_lse, 0, p.ws_lse_bytes, kBufferFormat);
       const int s_db = nks <= C::kDB ? C::kDB / nks : 1;
-      const int d_lo = kslot * s_db, d_hi = d_lo + s_db;   // this wave's d blocks
+      const int d_lo = kslot * s_db;   // this wave's d blocks d_lo + u, in o[u]
       if (sh_direct) {
         if (pend_ok) {
           const int srow = 2 * ql * p.Rcap + row;
@@ -1468,10 +1500,11 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
               float, __builtin_amdgcn_raw_buffer_load_b32(ws_lse_rsrc, srow * 4, 0, kDeviceCoherent));
           f32x4 xp[C::kDB];
 #pragma unroll
-          for (int db = 0; db < C::kDB; ++db)
-            if (db >= d_lo && db < d_hi)
-              xp[db] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                     ws_o_rsrc, (srow * D + 16 * db + 4 * lg) * 4, 0, kDeviceCoherent));
+          for (int u = 0; u < C::kDB; ++u)
+            if (u < s_db && d_lo < C::kDB)
+              xp[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                    ws_o_rsrc, (srow * D + 16 * (d_lo + u) + 4 * lg) * 4, 0,
+                                                    kDeviceCoherent));
           // this range's piece, then the next range's, as the merge of
           // pieces takes them
           float m = -INFINITY, z = 0.f, wa = 0.f, wb = 0.f;
@@ -1494,12 +1527,12 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
           const int pend_orow = (cur.b * p.C_max + tok) * p.Hq + cur.kvh * g + row - tok * g;
           float* dst = p.out + (size_t)pend_orow * D;
 #pragma unroll
-          for (int db = 0; db < C::kDB; ++db)
-            if (db >= d_lo && db < d_hi)
-            {
-              const f32x4 res = (o[db] * pend_inv * wa + wb * xp[db]) * inv_z;
-              if constexpr (NT) __builtin_nontemporal_store(res, reinterpret_cast<f32x4*>(dst + 16 * db + 4 * lg));
-              else *reinterpret_cast<f32x4*>(dst + 16 * db + 4 * lg) = res;
+          for (int u = 0; u < C::kDB; ++u)
+            if (u < s_db && d_lo < C::kDB) {
+              const f32x4 res = (o[u] * pend_inv * wa + wb * xp[u]) * inv_z;
+              f32x4* to = reinterpret_cast<f32x4*>(dst + 16 * (d_lo + u) + 4 * lg);
+              if constexpr (NT) __builtin_nontemporal_store(res, to);
+              else *to = res;
             }
           if (kslot == 0 && lg == 0) {
             const float res_lse = z > 0.f ? m + logf(z) : -INFINITY;
@@ -1514,10 +1547,10 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
             __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, pend_lse), ws_lse_rsrc, pend_row * 4, 0,
                                                   kDeviceCoherent);
 #pragma unroll
-          for (int db = 0; db < C::kDB; ++db)
-            if (db >= d_lo && db < d_hi)
-              __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, o[db] * pend_inv), ws_o_rsrc,
-                                                     (pend_row * D + 16 * db + 4 * lg) * 4, 0, kDeviceCoherent);
+          for (int u = 0; u < C::kDB; ++u)
+            if (u < s_db && d_lo < C::kDB)
+              __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, o[u] * pend_inv), ws_o_rsrc,
+                                                     (pend_row * D + 16 * (d_lo + u) + 4 * lg) * 4, 0, kDeviceCoherent);
         }
         // counted as in the loop: after every wave's stores, by the last wave
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
