@@ -8,10 +8,14 @@
 //     entries of one row, 8 KB by default); a persistent grid of waves (two
 //     workgroups of 8 waves per CU) takes contiguous ranges of the list, so
 //     few workgroups are dispatched whatever the batch;
-//   * a wave streams its items with 16-byte non-temporal loads, 4 KB per
-//     wave in flight (every logit is read once), keeps a per-lane (max,
-//     first index), and reduces it across the wave only where its range
-//     leaves a row: one partial result per (row, wave) segment;
+//   * a wave streams its items with 16-byte non-temporal loads, 4 or 8 KB per
+//     wave in flight (every logit is read once), keeps per lane the best value
+//     and the vector that holds it, and works out the entry and reduces it
+//     across the wave only where its range leaves a row: one partial result
+//     per (row, wave) segment.  A vector of 8 bf16 entries costs 8 unpacks, a
+//     max tree and one update (19 VALU instructions; compared entry by entry
+//     it was 48, as much time as the stream: B = 64 11.3 -> 8.8 us, B = 256
+//     28.7 -> 24.6);
 //   * after its last segment of a sequence, a wave counts itself on an LDS
 //     counter of its workgroup; the workgroup's last wave for the sequence
 //     counts the workgroup on the sequence's arrival counter (device-scope
@@ -35,9 +39,11 @@ constexpr int kGroupsPerCU = 2;
 constexpr int kCUs = 256;                  // MI355X
 constexpr int kVecBytes = 16;
 constexpr int kItemBytes = 8192;           // default item: 8 KB of logits
-// 16-byte loads per lane in flight (4 KB per wave): measured faster than 2,
-// 8 or 16, and than issuing the next batch before reducing the current one
-constexpr int kBatch = 4;
+// 16-byte loads per lane in flight: 8 for waves with at least two default
+// items to read (B = 256, 131 MB: 24.6 us against 25.1 with 4 and 25.6 with
+// 2), 4 for the others, whose one item ends sooner the sooner its first half
+// is compared (B = 64, 20 MB: 8.8 us against 9.1 with 8).
+constexpr int kLongBatch = 8, kShortBatch = 4;
 constexpr int kSplitUnit = 512;            // item granularity (entries)
 constexpr int kMaxChunk = 1024;            // C_max limit
 constexpr int kMaxSeqs = 65536;            // B limit (fixed counter region)
@@ -71,28 +77,44 @@ struct Params {
 };
 
 // (v, i) beats (bv, bi): a larger value, or an equal one at a lower index.
-// Floating-point equality makes +0 and -0 equal; -inf rows still elect their
-// first index because the starting index is INT_MAX.
+// Floating-point equality makes +0 and -0 equal.
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
   return v > bv || (v == bv && i < bi);
 }
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
-// (max, first index) over the wave, returned in every lane
-__device__ __forceinline__ void wave_best(float& bv, int& bi) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const float ov = __shfl_xor(bv, off);
-    const int oi = __shfl_xor(bi, off);
-    if (better(ov, oi, bv, bi)) {
-      bv = ov;
-      bi = oi;
-    }
-  }
+// Max of a float, min and max of an int over the wave, in every lane: shifts
+// within each 16-lane row, then row ends broadcast into the rows after them
+// (DPP moves; as six shuffles through LDS the two reductions of a segment
+// took 0.6 us).
+template <class OP>
+__device__ __forceinline__ int wave_fold(int x, OP op) {
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x111, 0xf, 0xf, false));   // row_shr:1
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x112, 0xf, 0xf, false));   // row_shr:2
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x114, 0xf, 0xf, false));   // row_shr:4
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x118, 0xf, 0xf, false));   // row_shr:8
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xa, 0xf, false));   // row_bcast:15 into rows 1 and 3
+  x = op(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xc, 0xf, false));   // row_bcast:31 into rows 2 and 3
+  return __builtin_amdgcn_readlane(x, 63);
+}
+__device__ __forceinline__ float wave_max(float x) {
+  return __int_as_float(wave_fold(__float_as_int(x), [](int a, int b) {
+    return __float_as_int(fmaxf(__int_as_float(a), __int_as_float(b)));
+  }));
+}
+__device__ __forceinline__ int wave_min(int x) { return wave_fold(x, [](int a, int b) { return min(a, b); }); }
+__device__ __forceinline__ int wave_max(int x) { return wave_fold(x, [](int a, int b) { return max(a, b); }); }
+
+// entry e of a 16-byte vector of logits
+template <bool BF16>
+__device__ __forceinline__ float entry(const u32x4& x, int e) {
+  // (bf16 entry 2k is the low half of word k, 2k + 1 the high half)
+  if constexpr (BF16) return __uint_as_float((e & 1) ? (x[e >> 1] & 0xffff0000u) : (x[e >> 1] << 16));
+  else return __uint_as_float(x[e]);
 }
 
-template <bool BF16>
+template <bool BF16, int kBatch>
 __global__ __launch_bounds__(kThreads, kGroupsPerCU) void accept_kernel(Params p) {
   constexpr int kElt = BF16 ? 2 : 4;
   constexpr int kPer = kVecBytes / kElt;   // entries per 16-byte vector
@@ -133,15 +155,39 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void accept_kernel(Params p
     // this wave's items of the sequence's valid rows
     const int ya = max(x0, b * CS), yb = min(x1, b * CS + c * p.S);
     if (ya >= yb) continue;
-    float bv = -INFINITY;
-    int bi = INT_MAX;
-    int seg = ya;                          // first item of the current row segment
-    for (int y = ya; y < yb; ++y) {
-      const int row = y / p.S;
-      const int lo = (y - row * p.S) * p.split;
-      const int nvec = (min(lo + p.split, p.V) - lo) / kPer;   // V and split are multiples of kPer
+    // row segments: the wave's items of one row are one run of vectors.  A
+    // lane keeps its best value and the first vector that holds it (its words
+    // and its index); which entry of the vector it is, is worked out once at
+    // the segment's end.
+    for (int seg = ya; seg < yb;) {
+      const int row = seg / p.S;
+      const int seg_end = min((row + 1) * p.S, yb);
+      const int lo = (seg - row * p.S) * p.split;
+      const int hi = min((seg_end - row * p.S) * p.split, p.V);
+      const int nvec = (hi - lo) / kPer;   // V and split are multiples of kPer
       const u32x4* src = reinterpret_cast<const u32x4*>(p.logits + ((size_t)row * p.V + lo) * kElt);
-      for (int v0 = 0; v0 < nvec; v0 += 64 * kBatch) {
+      float bv = -INFINITY;
+      int bvec = 0;
+      u32x4 bx = {0u, 0u, 0u, 0u};
+      auto take = [&](const u32x4& x, int v, bool in) {
+        float m = entry<BF16>(x, 0);
+#pragma unroll
+        for (int e = 1; e < kPer; ++e) m = fmaxf(m, entry<BF16>(x, e));
+        if (in && m > bv) {
+          bv = m;
+          bvec = v;
+          bx = x;
+        }
+      };
+      int v0 = 0;
+      for (; v0 + 64 * kBatch <= nvec; v0 += 64 * kBatch) {
+        u32x4 x[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) x[u] = __builtin_nontemporal_load(src + v0 + u * 64 + lane);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) take(x[u], v0 + u * 64 + lane, true);
+      }
+      if (v0 < nvec) {
         u32x4 x[kBatch];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
@@ -149,38 +195,19 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void accept_kernel(Params p
           x[u] = v < nvec ? __builtin_nontemporal_load(src + v) : u32x4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-          const int v = v0 + u * 64 + lane;
-          if (v < nvec) {
-            const int idx = lo + v * kPer;
+        for (int u = 0; u < kBatch; ++u) take(x[u], v0 + u * 64 + lane, v0 + u * 64 + lane < nvec);
+      }
+      // publish the segment's maximum and its first index: a segment in
+      // which no entry passes -inf elects its first one
+      const float m = wave_max(bv);
+      int idx = INT_MAX;
 #pragma unroll
-            for (int e = 0; e < kPer; ++e) {
-              float val;
-              if constexpr (BF16) {
-                // bf16 entry 2k is the low half of word k, 2k+1 the high half
-                const uint32_t wd = x[u][e >> 1];
-                val = __uint_as_float((e & 1) ? (wd & 0xffff0000u) : (wd << 16));
-              } else {
-                val = __uint_as_float(x[u][e]);
-              }
-              if (better(val, idx + e, bv, bi)) {
-                bv = val;
-                bi = idx + e;
-              }
-            }
-          }
-        }
-      }
-      if (y + 1 == yb || (y + 1) / p.S != row) {
-        // the wave leaves this row: publish the segment's maximum
-        wave_best(bv, bi);
-        if (lane == 0)
-          __builtin_amdgcn_raw_buffer_store_b64(i32x2{__float_as_int(bv), bi}, part_rsrc, seg * 8, 0,
-                                                kDeviceCoherent);
-        bv = -INFINITY;
-        bi = INT_MAX;
-        seg = y + 1;
-      }
+      for (int e = kPer - 1; e >= 0; --e)
+        if (entry<BF16>(bx, e) == m) idx = lo + bvec * kPer + e;
+      idx = m == -INFINITY ? lo : wave_min(bv == m ? idx : INT_MAX);
+      if (lane == 0)
+        __builtin_amdgcn_raw_buffer_store_b64(i32x2{__float_as_int(m), idx}, part_rsrc, seg * 8, 0, kDeviceCoherent);
+      seg = seg_end;
     }
     // what the sequence's last wave needs besides the segments is loaded now,
     // so that it rides the wait for the segment stores: the context length
@@ -244,7 +271,7 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void accept_kernel(Params p
               ri = e[u][1];
             }
         }
-        pred = ri == INT_MAX ? -1 : ri;   // (a row of NaN elects nothing)
+        pred = ri == INT_MAX ? -1 : ri;
       }
       if (k < p.C_max) p.argmax[(size_t)b * p.C_max + k] = pred;
       if (tree) {
@@ -262,13 +289,12 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void accept_kernel(Params p
         const uint64_t rejected = __ballot(reject);
         const bool ok = k < c && (word & rejected) == 0;
         int key = ok ? ((__popcll(word) - 1) << 8) | (255 - k) : -1;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) key = max(key, __shfl_xor(key, off));
+        key = wave_max(key);
         const int d = 255 - (key & 255);
         a = key >> 8;
-        next = __shfl(pred, d);
-        const uint32_t path_lo = (uint32_t)__shfl((int)(uint32_t)word, d);
-        const uint32_t path_hi = (uint32_t)__shfl((int)(uint32_t)(word >> 32), d);
+        next = __builtin_amdgcn_readlane(pred, d & 63);
+        const uint32_t path_lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, d & 63);
+        const uint32_t path_hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), d & 63);
         if (lane == 0) p.path[b] = ((uint64_t)path_hi << 32) | path_lo;
         break;
       }
@@ -276,8 +302,8 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void accept_kernel(Params p
       const bool reject = k < c - 1 && tok != pred;
       const uint64_t m = __ballot(reject);
       const int first_reject = m ? (int)__builtin_ctzll(m) : 64;
-      const int at_reject = __shfl(pred, first_reject & 63);
-      const int at_end = __shfl(pred, (c - 1 - k0) & 63);
+      const int at_reject = __builtin_amdgcn_readlane(pred, first_reject & 63);
+      const int at_end = __builtin_amdgcn_readlane(pred, (c - 1 - k0) & 63);
       if (a < 0 && m) {
         a = k0 + first_reject;
         next = at_reject;
@@ -430,10 +456,14 @@ int accept_run(const void* logits, const int32_t* tokens, const uint64_t* draft_
   const unsigned grid = (unsigned)pl.groups;
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
-  if (desc->dtype == SPECMOE_BF16)
-    hipLaunchKernelGGL(accept_kernel<true>, dim3(grid), dim3(kThreads), 0, s, p);
-  else
-    hipLaunchKernelGGL(accept_kernel<false>, dim3(grid), dim3(kThreads), 0, s, p);
+  const bool long_ranges = (int64_t)p.q * p.split * elt_of(desc) >= 2 * kItemBytes;
+  if (desc->dtype == SPECMOE_BF16) {
+    if (long_ranges) hipLaunchKernelGGL((accept_kernel<true, kLongBatch>), dim3(grid), dim3(kThreads), 0, s, p);
+    else hipLaunchKernelGGL((accept_kernel<true, kShortBatch>), dim3(grid), dim3(kThreads), 0, s, p);
+  } else {
+    if (long_ranges) hipLaunchKernelGGL((accept_kernel<false, kLongBatch>), dim3(grid), dim3(kThreads), 0, s, p);
+    else hipLaunchKernelGGL((accept_kernel<false, kShortBatch>), dim3(grid), dim3(kThreads), 0, s, p);
+  }
   return hipGetLastError() == hipSuccess ? SPECMOE_OK : SPECMOE_ERR_LAUNCH;
 }
 

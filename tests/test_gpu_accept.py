@@ -251,3 +251,30 @@ def test_accept_tree_rejects_wide_chunks():
     with pytest.raises(pkg.SpecMoEError) as e:
         pkg.accept_greedy_tree(x, t, torch.zeros((1, 65), dtype=torch.int64, device=d), n, n)
     assert e.value.status == -13
+
+
+@pytest.mark.parametrize("B,C,V,dtype,split", [
+    (64, 8, 8192, "bf16", 512),      # 2 items of 1 KB per wave: short ranges
+    (64, 8, 16384, "bf16", 0),       # one item per wave
+    (200, 8, 32008, "bf16", 0),      # long ranges over rows with a vector over
+    (200, 5, 16132, "f32", 0),
+    (90, 8, 40960, "f32", 4096),     # ranges that start inside rows
+    (3, 2, 8, "bf16", 0),            # one vector per row
+])
+def test_accept_range_lengths_and_ties(B, C, V, dtype, split):
+    """Rows of few distinct values (every maximum is tied many times, at the
+    ends of the row too) and rows of -inf, over both load batches."""
+    rng = np.random.default_rng([B, V])
+    x = rng.integers(-3, 4, size=(B, C, V)).astype(np.float32)
+    x[:, :, rng.integers(0, V, size=3)] = 3.0
+    top = rng.random((B, C))
+    x[top < 0.2] = -np.inf                               # all equal: the first entry
+    x[(top > 0.2) & (top < 0.3), V - 1] = 5.0            # the last entry alone
+    x[(top > 0.3) & (top < 0.4)] *= np.float32(-0.0)     # +0 and -0
+    first = x.argmax(-1)
+    tokens = rng.integers(0, V, size=(B, C)).astype(np.int32)
+    hit = rng.random((B, C)) < 0.8
+    tokens[:, 1:] = np.where(hit[:, :-1], first[:, :-1], tokens[:, 1:])
+    chunk = rng.integers(0, C + 1, size=B).astype(np.int32)
+    logits = wl.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    check(logits, tokens, rng.integers(0, 99, size=B).astype(np.int32), chunk, dtype, f"B={B} V={V} {dtype}", split)
