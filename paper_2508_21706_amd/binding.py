@@ -183,7 +183,32 @@ def workspace_status(workspace: Optional[torch.Tensor], stream: Optional[torch.c
     return st
 
 
+# The raw handle of a device's current stream, without the Stream object that
+# torch.cuda.current_stream builds (1.3 us a call).
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _raw_stream(t: torch.Tensor, stream: Optional[torch.cuda.Stream]) -> int:
+    """Handle of ``stream``, or of the current stream of ``t``'s GPU."""
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is not None:
+        return _current_raw_stream(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream
+
+
+def _empty(shape, dtype, device, stream: Optional[torch.cuda.Stream]) -> torch.Tensor:
+    """An output buffer from the launch stream's pool."""
+    if stream is None:   # the current stream's, as it is
+        return torch.empty(shape, dtype=dtype, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(shape, dtype=dtype, device=device)
+
+
 def _check(t: torch.Tensor, name: str, shape, dtype):
+    # the common case in one expression: a call checks up to nine tensors
+    if t.is_cuda and t.dtype is dtype and t.shape == shape and t.is_contiguous():
+        return
     if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if tuple(t.shape) != tuple(shape):
@@ -237,10 +262,9 @@ def verify_attn_noalloc(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.T
     _check(out, "out", (B, C_max, Hq, D), torch.float32)
     _check(lse, "lse", (B, C_max, Hq), torch.float32)
     desc = make_desc(B, Hq, Hkv, D, C_max, S_max, _dtype_code(q), grid_blocks)
-    s = stream if stream is not None else torch.cuda.current_stream(q.device)
     st = lib.specmoe_verify_attn_noalloc(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), ctx_lens.data_ptr(),
                                          chunk_lens.data_ptr(), float(scale), out.data_ptr(), lse.data_ptr(),
-                                         s.cuda_stream, ctypes.byref(desc))
+                                         _raw_stream(q, stream), ctypes.byref(desc))
     if st != 0:
         raise SpecMoEError(st, status_str(st))
     return out, lse
@@ -317,35 +341,34 @@ def _call(q, k_cache, v_cache, ctx_lens, chunk_lens, draft_mask, scale, out, lse
         l = ctx_lens.cpu()
         if (c < 0).any() or (c > C_max).any() or (l < 0).any() or (l + c > S_max).any():
             raise ValueError("lengths break 0 <= c_b <= C_max, l_b >= 0, l_b + c_b <= S_max")
-    s = stream if stream is not None else torch.cuda.current_stream(q.device)
-    with torch.cuda.stream(s):   # outputs from the launch stream's pool
-        if out is None:
-            out = torch.empty((B, C_max, Hq, D), dtype=torch.float32, device=q.device)
-        if lse is None:
-            lse = torch.empty((B, C_max, Hq), dtype=torch.float32, device=q.device)
+    if out is None:
+        out = _empty((B, C_max, Hq, D), torch.float32, q.device, stream)
+    if lse is None:
+        lse = _empty((B, C_max, Hq), torch.float32, q.device, stream)
     _check(out, "out", (B, C_max, Hq, D), torch.float32)
     _check(lse, "lse", (B, C_max, Hq), torch.float32)
     desc = make_desc(B, Hq, Hkv, D, C_max, S_max, _dtype_code(q), grid_blocks, flags)
     if B == 0:
         return out, lse
     if workspace is None:
-        workspace = alloc_workspace(desc, q.device, s)
+        workspace = alloc_workspace(desc, q.device, stream)
     desc.workspace = workspace.data_ptr()
-    desc.workspace_bytes = workspace.numel() * workspace.element_size()
+    desc.workspace_bytes = workspace.nbytes
+    raw = _raw_stream(q, stream)
     if paged is not None:
         st = lib.specmoe_verify_attn_paged(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(),
                                            block_table.data_ptr(), ctx_lens.data_ptr(), chunk_lens.data_ptr(),
                                            draft_mask.data_ptr() if draft_mask is not None else None,
-                                           float(scale), out.data_ptr(), lse.data_ptr(), s.cuda_stream,
+                                           float(scale), out.data_ptr(), lse.data_ptr(), raw,
                                            ctypes.byref(desc), ctypes.byref(paged))
     elif draft_mask is None:
         st = lib.specmoe_verify_attn(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(),
                                      ctx_lens.data_ptr(), chunk_lens.data_ptr(), float(scale),
-                                     out.data_ptr(), lse.data_ptr(), s.cuda_stream, ctypes.byref(desc))
+                                     out.data_ptr(), lse.data_ptr(), raw, ctypes.byref(desc))
     else:
         st = lib.specmoe_verify_attn_tree(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(),
                                           ctx_lens.data_ptr(), chunk_lens.data_ptr(), draft_mask.data_ptr(),
-                                          float(scale), out.data_ptr(), lse.data_ptr(), s.cuda_stream,
+                                          float(scale), out.data_ptr(), lse.data_ptr(), raw,
                                           ctypes.byref(desc))
     if st != 0:
         raise SpecMoEError(st, status_str(st))
@@ -406,9 +429,8 @@ def compact_accepted_kv(k_cache: torch.Tensor, v_cache: torch.Tensor, ctx_lens: 
     _check(ctx_lens, "ctx_lens", (B,), torch.int32)
     _check(path, "path", (B,), path.dtype if path.dtype in (torch.int64, torch.uint64) else torch.int64)
     desc = make_desc(B, Hkv, Hkv, D, 1, S_max, _dtype_code(k_cache))
-    s = stream if stream is not None else torch.cuda.current_stream(k_cache.device)
     st = lib.specmoe_compact_accepted_kv(k_cache.data_ptr(), v_cache.data_ptr(), ctx_lens.data_ptr(), path.data_ptr(),
-                                         s.cuda_stream, ctypes.byref(desc))
+                                         _raw_stream(k_cache, stream), ctypes.byref(desc))
     if st != 0:
         raise SpecMoEError(st, status_str(st))
 
@@ -435,34 +457,32 @@ def accept_greedy(logits: torch.Tensor, tokens: torch.Tensor, ctx_lens: torch.Te
     dev = logits.device
     if out is None:
         out = {}
-    for key, shape in (("argmax", (B, C_max)), ("accepted", (B,)), ("next_token", (B,))):
-        if key not in out:
-            out[key] = torch.empty(shape, dtype=torch.int32, device=dev)
-    if not in_place and "new_ctx_lens" not in out:
-        out["new_ctx_lens"] = torch.empty((B,), dtype=torch.int32, device=dev)
+    for key in ("argmax", "accepted", "next_token", "new_ctx_lens"):
+        if key not in out and not (in_place and key == "new_ctx_lens"):
+            out[key] = torch.empty((B, C_max) if key == "argmax" else (B,), dtype=torch.int32, device=dev)
     if in_place:
         out["new_ctx_lens"] = ctx_lens
     _check(out["argmax"], "argmax", (B, C_max), torch.int32)
     for k in ("accepted", "next_token", "new_ctx_lens"):
         _check(out[k], k, (B,), torch.int32)
     desc = accept_desc(B, C_max, V, _dtype_code(logits), split)
-    s = stream if stream is not None else torch.cuda.current_stream(dev)
     if B == 0:
         return out
     if workspace is None:
-        workspace = alloc_accept_workspace(desc, dev, s)
+        workspace = alloc_accept_workspace(desc, dev, stream)
     desc.workspace = workspace.data_ptr()
-    desc.workspace_bytes = workspace.numel() * workspace.element_size()
+    desc.workspace_bytes = workspace.nbytes
+    raw = _raw_stream(logits, stream)
     if _tree is None:
         st = lib.specmoe_accept_greedy(logits.data_ptr(), tokens.data_ptr(), ctx_lens.data_ptr(),
                                        chunk_lens.data_ptr(), out["argmax"].data_ptr(), out["accepted"].data_ptr(),
-                                       out["next_token"].data_ptr(), out["new_ctx_lens"].data_ptr(), s.cuda_stream,
+                                       out["next_token"].data_ptr(), out["new_ctx_lens"].data_ptr(), raw,
                                        ctypes.byref(desc))
     else:
         st = lib.specmoe_accept_greedy_tree(logits.data_ptr(), tokens.data_ptr(), _tree[0].data_ptr(),
                                             ctx_lens.data_ptr(), chunk_lens.data_ptr(), out["argmax"].data_ptr(),
                                             out["accepted"].data_ptr(), out["next_token"].data_ptr(),
-                                            out["new_ctx_lens"].data_ptr(), _tree[1].data_ptr(), s.cuda_stream,
+                                            out["new_ctx_lens"].data_ptr(), _tree[1].data_ptr(), raw,
                                             ctypes.byref(desc))
     if st != 0:
         raise SpecMoEError(st, status_str(st))
