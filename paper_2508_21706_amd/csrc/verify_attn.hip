@@ -118,7 +118,7 @@ constexpr int kDeviceCoherent = 16;   // SC1
 // policy the whole launch ran 6-11% slower.
 constexpr int kStreaming = 2;
 // kernel variants (template argument MODE)
-constexpr int kModePlain = 0, kModeHold = 1, kModeNt = 2;
+constexpr int kModePlain = 0, kModeHold = 1, kModeThrough = 2;
 constexpr int kBufferFormat = 0x00020000;   // raw 32-bit buffer descriptor word 3
 
 struct Params {
@@ -330,9 +330,12 @@ __device__ __forceinline__ int tile_cost(const Params& p, uint32_t s) {
 // last tile), so ranges that cross more unit boundaries get fewer tiles.  A
 // range that starts inside a unit pays for that unit's end.  (Measured: on
 // B = 64 with chunks of 5 and 4 query heads per KV head a unit end holds a
-// workgroup ~1.6 us and its start ~0.6 us, against ~2.2 us per tile.)
+// workgroup ~1.6 us and its start ~0.6 us, against ~2.2 us per tile; a fit
+// over eight splits of the tree workload, four row blocks per unit, gives
+// 2.2 us per unit and 2.3 per tile: with 3 + 6 for it, not 6 + 0, 77.9 -> 77.0
+// us per call, ragged chunks 123.1 -> 122.5.)
 constexpr int kStartSplit = 3, kEndSplit = 9;   // units of one or two row blocks
-constexpr int kStartRest = 6, kEndRest = 0;     // larger units
+constexpr int kStartRest = 3, kEndRest = 6;     // larger units
 constexpr int kExtraMax = kStartSplit + kEndSplit > kStartRest + kEndRest ? kStartSplit + kEndSplit : kStartRest + kEndRest;
 __device__ __forceinline__ bool split_unit(const Params& p, uint32_t s) { return seq_c(s) * p.g <= 2 * kBlk; }
 __device__ __forceinline__ int start_cost(const Params& p, uint32_t s) {
@@ -383,6 +386,18 @@ struct Cursor {
   uint32_t s;
 };
 
+// Four results, the i-th value of `out` on.  THROUGH: with device scope, so
+// that they leave the L2 at once (32-bit byte offsets, host check).
+template <bool THROUGH>
+__device__ __forceinline__ void store_out(const Params& p, size_t i, f32x4 x) {
+  if constexpr (THROUGH)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, x),
+                                           __builtin_amdgcn_make_buffer_rsrc(p.out, 0, 0xffffffffu, kBufferFormat),
+                                           (int)((uint32_t)i * 4u), 0, kDeviceCoherent);
+  else
+    *reinterpret_cast<f32x4*>(p.out + i) = x;
+}
+
 // e^(a - b) for a <= b: weights of log-sum-exp pieces
 __device__ __forceinline__ float exp_diff(float a, float b) { return __builtin_amdgcn_exp2f((a - b) * kLog2e); }
 // acc + w x in one rounding: the same bits wherever pieces are merged
@@ -400,7 +415,7 @@ __device__ __forceinline__ f32x4 add_weighted(f32x4 acc, float w, f32x4 x) {
 // once and each piece weighed once, with the hardware's exponential (three
 // items, four pieces and two library exponentials per piece: B = 4, eight
 // pieces per unit, 17.1 us per call, now 15.5).  Unit u is described by e_u = {unit, qf, ql}.
-template <int D, bool NT>
+template <int D, bool THROUGH>
 __device__ __forceinline__ void merge_units(const Params& p, const uint32_t* seqs, int ctid, i32x4 e_a,
                                          i32x4 e_b, bool has_a, bool has_b) {
   const __amdgpu_buffer_rsrc_t ws_o_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_o, 0, p.ws_o_bytes, kBufferFormat);
@@ -492,13 +507,8 @@ __device__ __forceinline__ void merge_units(const Params& p, const uint32_t* seq
       // (z = 0: a row that sees no key in any piece)
       const f32x4 res = acc[it] * (z[it] > 0.f ? 1.f / z[it] : 0.f);
       const float res_lse = z[it] > 0.f ? m[it] + logf(z[it]) : -INFINITY;
-      if constexpr (NT) {
-        __builtin_nontemporal_store(res, reinterpret_cast<f32x4*>(p.out + orow[it] * D + d0[it]));
-        if (d0[it] == 0) __builtin_nontemporal_store(res_lse, p.lse + orow[it]);
-      } else {
-        *reinterpret_cast<f32x4*>(p.out + orow[it] * D + d0[it]) = res;
-        if (d0[it] == 0) p.lse[orow[it]] = res_lse;
-      }
+      store_out<THROUGH>(p, orow[it] * D + d0[it], res);
+      if (d0[it] == 0) p.lse[orow[it]] = res_lse;
     }
   }
   if (ctid == 0) {   // ready for the next call
@@ -511,13 +521,12 @@ __device__ __forceinline__ void merge_units(const Params& p, const uint32_t* seq
 // chain mask.  PAGED: the KV cache is a pool of pages found through a block
 // table.  MODE kModeHold (launches whose units have at most two 16-row
 // blocks): the piece of a range's first segment is held in LDS until three
-// quarters into the range.  MODE kModeNt: results are stored with the
-// non-temporal policy (launches with many units per workgroup and a large
-// output).
+// quarters into the range.  MODE kModeThrough: results are stored with device
+// scope (launches with many units per workgroup and a large output).
 template <int ELT, int D, bool TREE, bool PAGED, int MODE>
 __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
   constexpr bool HOLD = MODE == kModeHold;
-  constexpr bool NT = MODE == kModeNt;
+  constexpr bool THROUGH = MODE == kModeThrough;
   constexpr bool W16 = ELT != kF32;   // 16-bit elements
   using C = Cfg<W16, D>;
   __shared__ __attribute__((aligned(16))) char smem[kStages * C::kStage];
@@ -1050,20 +1059,11 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       const int s_db = nks <= C::kDB ? C::kDB / nks : 1;
       const int d_lo = kslot * s_db;   // this wave's d blocks d_lo + u, in o[u]
       if (pend_whole) {
-        float* dst = p.out + (size_t)pend_row * D;
-        if (kslot == 0 && lg == 0) {
-          if constexpr (NT) __builtin_nontemporal_store(pend_lse, p.lse + pend_row);
-          else p.lse[pend_row] = pend_lse;
-        }
+        if (kslot == 0 && lg == 0) p.lse[pend_row] = pend_lse;
 #pragma unroll
         for (int u = 0; u < C::kDB; ++u)
-          if (u < s_db && d_lo < C::kDB) {
-            f32x4* to = reinterpret_cast<f32x4*>(dst + 16 * (d_lo + u) + 4 * lg);
-            if constexpr (NT)
-              __builtin_nontemporal_store(o[u] * pend_inv, to);
-            else
-              *to = o[u] * pend_inv;
-          }
+          if (u < s_db && d_lo < C::kDB)
+            store_out<THROUGH>(p, (size_t)pend_row * D + 16 * (d_lo + u) + 4 * lg, o[u] * pend_inv);
       } else {
         // read by another workgroup, possibly on another XCD
         const __amdgpu_buffer_rsrc_t ws_o_rsrc =
@@ -1532,20 +1532,12 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
           const float inv_z = z > 0.f ? 1.f / z : 0.f;
           // (cur is still the last tile's cursor)
           const int pend_orow = (cur.b * p.C_max + tok) * p.Hq + cur.kvh * g + row - tok * g;
-          float* dst = p.out + (size_t)pend_orow * D;
 #pragma unroll
           for (int u = 0; u < C::kDB; ++u)
-            if (u < s_db && d_lo < C::kDB) {
-              const f32x4 res = add_weighted(add_weighted(f32x4{0.f, 0.f, 0.f, 0.f}, wa, o[u] * pend_inv), wb, xp[u]) * inv_z;
-              f32x4* to = reinterpret_cast<f32x4*>(dst + 16 * (d_lo + u) + 4 * lg);
-              if constexpr (NT) __builtin_nontemporal_store(res, to);
-              else *to = res;
-            }
-          if (kslot == 0 && lg == 0) {
-            const float res_lse = z > 0.f ? m + logf(z) : -INFINITY;
-            if constexpr (NT) __builtin_nontemporal_store(res_lse, p.lse + pend_orow);
-            else p.lse[pend_orow] = res_lse;
-          }
+            if (u < s_db && d_lo < C::kDB)
+              store_out<THROUGH>(p, (size_t)pend_orow * D + 16 * (d_lo + u) + 4 * lg,
+                                 add_weighted(add_weighted(f32x4{0.f, 0.f, 0.f, 0.f}, wa, o[u] * pend_inv), wb, xp[u]) * inv_z);
+          if (kslot == 0 && lg == 0) p.lse[pend_orow] = z > 0.f ? m + logf(z) : -INFINITY;
         }
         if (ctid == 0) __hip_atomic_store(p.counters + u, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       } else {
@@ -1612,7 +1604,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
   {
     const int f0 = sh_flag[0], f1 = sh_flag[1];
     if (f0 || f1)
-      merge_units<D, NT>(p, seqs, ctid, sh_share[f0 ? f0 - 1 : 0], sh_share[f1 ? f1 - 1 : 0], f0 != 0, f1 != 0);
+      merge_units<D, THROUGH>(p, seqs, ctid, sh_share[f0 ? f0 - 1 : 0], sh_share[f1 ? f1 - 1 : 0], f0 != 0, f1 != 0);
   }
   report_give_up(gave_up);
 }
@@ -1689,16 +1681,19 @@ Plan make_plan(const specmoe_verify_desc* d) {
   return pl;
 }
 
-// Results (out and lse) are stored write-back, except in launches with both
-// many units per workgroup (at least kNtUnitsPerWg) and a large output (at
-// least kNtOutBytes), where the workgroups store results many times while the
-// K/V stream runs: there the non-temporal policy measured faster (B = 256, 8
-// KV heads, 16-33 MB of output: 2-7%; B = 128, 10.5 MB: 1.4%), while launches
-// with fewer, larger units (ragged chunks, tree drafts, B = 64) or a small
-// output (one-token decode) were 1-5% slower with it.  Launches that hold
-// their first piece in LDS keep that variant.
-constexpr int kNtUnitsPerWg = 4;
-constexpr size_t kNtOutBytes = (size_t)8 << 20;
+// Results are stored write-back, except in launches with both many units per
+// workgroup (at least kThroughUnits) and a large output (at least
+// kThroughBytes), where the workgroups store results many times while the K/V
+// stream runs: HBM serves single lines written between its reads poorly (a
+// probe that streams 2.7 GB takes 70 us longer with 34 MB of write-back stores
+// along the way, 58 with non-temporal and 49 with device-scope ones; 16-18 with
+// any of them at its end).  B = 256, 8 KV heads, 34 MB of output: 466 us
+// write-back, 449 non-temporal, 442 device scope.  Launches with fewer, larger
+// units (ragged chunks, tree drafts, B = 64) or a small output (one-token
+// decode) are 1-5% slower with either policy.  Launches that hold their first
+// piece in LDS keep that variant.
+constexpr int kThroughUnits = 4;
+constexpr size_t kThroughBytes = (size_t)8 << 20;
 
 template <int ELT, int D, bool TREE, bool PAGED>
 void launch(Params p, const Plan& pl, hipStream_t stream) {
@@ -1724,12 +1719,13 @@ void launch(Params p, const Plan& pl, hipStream_t stream) {
     if (TREE) s.draft_mask = p.draft_mask + (size_t)b0 * p.C_max;
     s.out = p.out + (size_t)b0 * p.C_max * p.Hq * D;
     s.lse = p.lse + (size_t)b0 * p.C_max * p.Hq;
-    const bool nt = s.B * p.Hkv >= kNtUnitsPerWg * pl.P &&
-                    (size_t)s.B * p.C_max * p.Hq * (D + 1) * sizeof(float) >= kNtOutBytes;
+    const size_t out_bytes = (size_t)s.B * p.C_max * p.Hq * D * sizeof(float);
+    const bool through = s.B * p.Hkv >= kThroughUnits * pl.P && out_bytes / D * (D + 1) >= kThroughBytes &&
+                         out_bytes < ((size_t)1 << 32);   // (32-bit offsets)
     if (hold)
       hipLaunchKernelGGL((verify_attn_kernel<ELT, D, TREE, PAGED, kModeHold>), dim3(pl.P), dim3(kThreads), 0, stream, s);
-    else if (nt)
-      hipLaunchKernelGGL((verify_attn_kernel<ELT, D, TREE, PAGED, kModeNt>), dim3(pl.P), dim3(kThreads), 0, stream, s);
+    else if (through)
+      hipLaunchKernelGGL((verify_attn_kernel<ELT, D, TREE, PAGED, kModeThrough>), dim3(pl.P), dim3(kThreads), 0, stream, s);
     else
       hipLaunchKernelGGL((verify_attn_kernel<ELT, D, TREE, PAGED, kModePlain>), dim3(pl.P), dim3(kThreads), 0, stream, s);
   }
