@@ -321,8 +321,8 @@ __device__ __forceinline__ int seq_tiles(uint32_t s) {
 // The weights follow measured tile times (ragged chunks, 1-7 row blocks:
 // 2.7, 3.1 and 3.3 us per tile for 1-2, 3-4 and 5-7 blocks).
 constexpr int kTileCost = 10;
-__device__ __forceinline__ int tile_cost(const Params& p, uint32_t s) {
-  return p.flat ? 1 : kTileCost + (seq_c(s) * p.g + kBlk - 1) / kBlk;
+__device__ __forceinline__ int tile_cost(const Params& p, uint32_t s, int whole) {
+  return whole || p.flat ? 1 : kTileCost + (seq_c(s) * p.g + kBlk - 1) / kBlk;
 }
 // Extra costs of a unit: at its start (a first tile that is mostly partial,
 // the switch of Q) and at its end (the result's stores and, for units of one
@@ -338,16 +338,32 @@ constexpr int kStartSplit = 3, kEndSplit = 9;   // units of one or two row block
 constexpr int kStartRest = 3, kEndRest = 6;     // larger units
 constexpr int kExtraMax = kStartSplit + kEndSplit > kStartRest + kEndRest ? kStartSplit + kEndSplit : kStartRest + kEndRest;
 __device__ __forceinline__ bool split_unit(const Params& p, uint32_t s) { return seq_c(s) * p.g <= 2 * kBlk; }
-__device__ __forceinline__ int start_cost(const Params& p, uint32_t s) {
-  return p.flat ? 0 : split_unit(p, s) ? kStartSplit : kStartRest;
+__device__ __forceinline__ int start_cost(const Params& p, uint32_t s, int whole) {
+  return whole || p.flat ? 0 : split_unit(p, s) ? kStartSplit : kStartRest;
 }
 __device__ __forceinline__ int end_cost(const Params& p, uint32_t s) {
   return p.flat ? 0 : split_unit(p, s) ? kEndSplit : kEndRest;
 }
+// Launches of few units (at most half the workgroups, one sequence per lane of
+// the scheduling wave): ranges are cut inside units only, `whole` tiles each,
+// so that no workgroup ends two units or holds two pieces: a second unit in a
+// range costs its end (1.2 us), and often the publication and merge of a
+// second piece, as much as one or two tiles of a launch that has two to
+// twenty per workgroup.  `whole` is the smallest that leaves at most one range
+// per workgroup, of kWholeTries from the even share on (past those the uneven
+// last ranges of units waste more), but at least kWholeMin (ranges of one tile
+// pay more for their merge than they save), and kWholeUnit where that makes
+// units whole on average.  Against equal cost: 8 KV heads, B = 1 with 300
+// tokens 12.4 -> 10.5 us, B = 8 with 512-2048 21.9 -> 19.4, B = 16 with 300-900
+// 20.8 -> 18.2, B = 2 with 16k 33.7 -> 31.0, B = 4 with 20-30k 72.3 -> 71.2;
+// B = 4 with 512-2048 (two tiles per range either way) 15.5 -> 15.6.
+constexpr int kWholeUnit = 3, kWholeMin = 2, kWholeTries = 4;
 // cost of one unit (one KV head) of a sequence with packed lengths s: its n
-// tiles, its start and its end
-__device__ __forceinline__ int unit_cost(const Params& p, int n, uint32_t s) {
-  return n > 0 ? n * tile_cost(p, s) + start_cost(p, s) + end_cost(p, s) : 0;
+// tiles, its start and its end; with `whole`, its tiles rounded up to whole
+// ranges
+__device__ __forceinline__ int unit_cost(const Params& p, int n, uint32_t s, int whole) {
+  if (whole) return (n + whole - 1) / whole * whole;
+  return n > 0 ? n * tile_cost(p, s, 0) + start_cost(p, s, 0) + end_cost(p, s) : 0;
 }
 
 // Tile schedule shared by every workgroup of a launch.  The tiles of all
@@ -368,7 +384,7 @@ __device__ __forceinline__ int unit_cost(const Params& p, int n, uint32_t s) {
 // 4.0 us (B = 4, 24 MB of K and V: 19.3 -> 17.5 us per call; B = 64, 347 MB:
 // 63.8 -> 63.2 us, as the stream makes up for most of it).
 struct Sched {
-  int N, Pe;
+  int N, Pe, whole;
   uint32_t Wt, width, longer;
   __device__ uint32_t bound(int q) const { return (uint32_t)q * width + min((uint32_t)q, longer); }   // range q's first cost
   // range of the tile that starts at cost c
@@ -602,7 +618,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     auto add = [&](uint32_t s) {     // (s = 0: no tiles, no cost)
       const int n = seq_tiles<C>(s);
       my_tiles += n;
-      my_cost += unit_cost(p, n, s);
+      my_cost += unit_cost(p, n, s, 0);
     };
     if (per == 1) {
       if (lane < B) {
@@ -623,11 +639,34 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
         }
       }
     }
-    const int incl = wave_scan(my_tiles), cincl = wave_scan(my_cost);
+    const int incl = wave_scan(my_tiles);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    sc.N = total * Hkv;   // tiles of all units (< 2^30, host check)
+    // few units: ranges of `whole` tiles of one unit each, if a small enough
+    // one leaves at most P ranges
+    sc.whole = 0;
+    int cincl = 0;
+    if (per == 1 && !p.flat) {
+      const int units = __builtin_popcountll(__ballot(my_tiles > 0)) * Hkv;
+      if (units > 0 && 2 * units <= p.P) {
+        int t = sc.N <= kWholeUnit * units ? kWholeUnit : kWholeMin;
+        if (sc.N > t * p.P) t = (sc.N + p.P - 1) / p.P;
+        for (int tries = 0; tries < kWholeTries; ++tries, ++t) {
+          const int k = (my_tiles + t - 1) / t;   // ranges per unit
+          const int kincl = wave_scan(k);
+          if (__builtin_amdgcn_readlane(kincl, 63) * Hkv <= p.P) {
+            sc.whole = t;
+            my_cost = k * t;
+            cincl = kincl * t;
+            break;
+          }
+        }
+      }
+    }
+    if (!sc.whole) cincl = wave_scan(my_cost);
     // exclusive prefixes: those of sequence b_lo (the totals in lanes without
     // sequences)
     const int ex = incl - my_tiles, cex = cincl - my_cost;
-    const int total = __builtin_amdgcn_readlane(incl, 63);
     if (per > 1) {
       int run = ex, crun = cex;
       for (int b = b_lo; b < b_hi; ++b) {
@@ -636,7 +675,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
         pref[b] = run;
         cpref[b] = crun;
         run += n;
-        crun += unit_cost(p, n, s);
+        crun += unit_cost(p, n, s, sc.whole);
       }
     }
     if (lane < kStages) {
@@ -651,10 +690,10 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     // every tile costs at most w_hi with its unit's start and end, so with at
     // most Wt / w_hi ranges (and at least one when there are tiles) no range
     // is empty
-    sc.N = total * Hkv;   // tiles of all units (< 2^30, host check)
     sc.Wt = (uint32_t)Hkv * (uint32_t)__builtin_amdgcn_readlane(cincl, 63);
     const uint32_t w_hi = p.flat ? 1 : kTileCost + (p.C_max * g + kBlk - 1) / kBlk + kExtraMax;
-    sc.Pe = sc.Wt >= (uint32_t)p.P * w_hi ? p.P : sc.N > 0 ? max((int)(sc.Wt / w_hi), 1) : 0;
+    if (sc.whole) sc.Pe = (int)(sc.Wt / (uint32_t)sc.whole);
+    else sc.Pe = sc.Wt >= (uint32_t)p.P * w_hi ? p.P : sc.N > 0 ? max((int)(sc.Wt / w_hi), 1) : 0;
     sc.width = sc.Wt / (uint32_t)max(sc.Pe, 1);
     sc.longer = sc.Wt - sc.width * (uint32_t)sc.Pe;
     // The sequence whose units hold cost X < Wt: the last one with Hkv
@@ -685,7 +724,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       a.n = seq_tiles<C>(a.s);
       a.t0 *= Hkv;
       a.c0 *= (uint32_t)Hkv;
-      a.U = (uint32_t)unit_cost(p, a.n, a.s);
+      a.U = (uint32_t)unit_cost(p, a.n, a.s, sc.whole);
       return a;
     };
     if (pid < sc.Pe) {
@@ -694,7 +733,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       At f = seq_at(X);
       uint32_t kvh = (X - f.c0) / f.U;
       uint32_t cf = f.c0 + kvh * f.U;
-      const uint32_t w = (uint32_t)tile_cost(p, f.s), S = (uint32_t)start_cost(p, f.s), r = X - cf;
+      const uint32_t w = (uint32_t)tile_cost(p, f.s, sc.whole), S = (uint32_t)start_cost(p, f.s, sc.whole), r = X - cf;
       uint32_t j = r == 0 ? 0 : r <= S ? 1 : (r - S + w - 1) / w;
       // (rounded up to a unit's end: the next unit's first tile)
       int g0 = f.t0 + (int)kvh * f.n + min((int)j, f.n);
@@ -711,13 +750,13 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       const At e = seq_at(Y);
       const uint32_t kvl = (Y - e.c0) / e.U;
       const uint32_t cl = e.c0 + kvl * e.U;
-      const uint32_t wl = (uint32_t)tile_cost(p, e.s), Sl = (uint32_t)start_cost(p, e.s), rl = Y - cl;
+      const uint32_t wl = (uint32_t)tile_cost(p, e.s, sc.whole), Sl = (uint32_t)start_cost(p, e.s, sc.whole), rl = Y - cl;
       const int jl = rl < Sl + wl ? 0 : min((int)((rl - Sl) / wl), e.n - 1);
       const int g1 = e.t0 + (int)kvl * e.n + jl + 1;
       if (lane == 0) {
         sh_sched[1] = i32x4{g1, f.b, (int)kvh, (int)j};
         sh_sched[2] = i32x4{(int)f.s, (int)cf, e.b, (int)kvl};
-        sh_sched[3] = i32x4{(int)e.s, (int)cl, g0, 0};
+        sh_sched[3] = i32x4{(int)e.s, (int)cl, g0, sc.whole};
       }
     }
     if (lane == 0) sh_sched[0] = i32x4{sc.Pe, (int)sc.width, (int)sc.longer, sc.N};
@@ -740,6 +779,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
   first.kvh = uniform(sw1[2]);
   first.j = uniform(sw1[3]);
   first.s = (uint32_t)uniform(sw2[0]);
+  sc.whole = uniform(sw3[3]);
   // the first tile of unit (b, kvh) after cursor cu's unit
   auto next_unit = [&](Cursor& cu) {
     cu.j = 0;
@@ -1019,7 +1059,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       const int n = seq_tiles<C>(s);
       if (lane == 0)
         sh_share[k] = i32x4{k == 0 ? first.b * Hkv + first.kvh : uniform(sw2[2]) * Hkv + uniform(sw2[3]), sc.owner(c),
-                            sc.owner(n > 1 ? c + start_cost(p, s) + (n - 1) * tile_cost(p, s) : c), 0};
+                            sc.owner(n > 1 ? c + start_cost(p, s, sc.whole) + (n - 1) * tile_cost(p, s, sc.whole) : c), 0};
     }
   }
 #pragma unroll

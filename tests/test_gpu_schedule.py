@@ -67,3 +67,13 @@ def test_no_sequence_takes_a_step():
         out, lse = nan_outputs(70, 2, 4, 64)
         pkg.verify_attn(q, k, k, zeros + 9, zeros, 0.125, out=out, lse=lse, grid_blocks=grid)
         assert (out == 0).all() and (lse == -np.inf).all()
+
+
+@pytest.mark.parametrize("grid", [4, 8, 9, 14, 15, 24, 40, 256])
+@pytest.mark.parametrize("ctx", [[0, 61, 2000, 700], [1100, 3, 64, 128], [60, 61, 100, 20]])
+def test_ranges_inside_units(ctx, grid):
+    """Few units: ranges of a fixed number of tiles inside units, from the
+    first grid with two workgroups per unit (8) over those where no small
+    number leaves a range per workgroup to one with whole units."""
+    inp = _custom(4, 2, 1, 128, "f32", ctx, [2, 1, 2, 2], 2)   # 64-key tiles
+    check_case(inp, "f32", f"ctx={ctx}", grid_blocks=grid)
