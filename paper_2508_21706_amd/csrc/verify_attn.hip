@@ -1671,6 +1671,10 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       }
     }
   }
+  if (n_pub == 0) {   // whole units only
+    report_give_up(gave_up);
+    return;
+  }
   cbar();
   {
     const int f0 = sh_flag[0], f1 = sh_flag[1];
