@@ -197,14 +197,27 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void accept_kernel(Params p
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) take(x[u], v0 + u * 64 + lane, v0 + u * 64 + lane < nvec);
       }
-      // publish the segment's maximum and its first index: a segment in
-      // which no entry passes -inf elects its first one
+      // publish the segment's maximum and its first index
       const float m = wave_max(bv);
       int idx = INT_MAX;
+      if (m > -INFINITY) {
 #pragma unroll
-      for (int e = kPer - 1; e >= 0; --e)
-        if (entry<BF16>(bx, e) == m) idx = lo + bvec * kPer + e;
-      idx = m == -INFINITY ? lo : wave_min(bv == m ? idx : INT_MAX);
+        for (int e = kPer - 1; e >= 0; --e)
+          if (entry<BF16>(bx, e) == m) idx = lo + bvec * kPer + e;
+        idx = wave_min(bv == m ? idx : INT_MAX);
+      } else {
+        // no entry passes -inf: the first -inf is looked up (a masked range
+        // holds it in its first vector), NaNs elect nothing
+        for (int w0 = 0; w0 < nvec && idx == INT_MAX; w0 += 64) {
+          const int v = w0 + lane;
+          const u32x4 x = src[min(v, nvec - 1)];
+          int at = INT_MAX;
+#pragma unroll
+          for (int e = kPer - 1; e >= 0; --e)
+            if (v < nvec && entry<BF16>(x, e) == -INFINITY) at = lo + v * kPer + e;
+          idx = wave_min(at);
+        }
+      }
       if (lane == 0)
         __builtin_amdgcn_raw_buffer_store_b64(i32x2{__float_as_int(m), idx}, part_rsrc, seg * 8, 0, kDeviceCoherent);
       seg = seg_end;
@@ -271,7 +284,7 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void accept_kernel(Params p
               ri = e[u][1];
             }
         }
-        pred = ri == INT_MAX ? -1 : ri;
+        pred = ri == INT_MAX ? -1 : ri;   // (a row of NaN elects nothing)
       }
       if (k < p.C_max) p.argmax[(size_t)b * p.C_max + k] = pred;
       if (tree) {

@@ -278,3 +278,28 @@ def test_accept_range_lengths_and_ties(B, C, V, dtype, split):
     chunk = rng.integers(0, C + 1, size=B).astype(np.int32)
     logits = wl.f32_to_bf16_bits(x) if dtype == "bf16" else x
     check(logits, tokens, rng.integers(0, 99, size=B).astype(np.int32), chunk, dtype, f"B={B} V={V} {dtype}", split)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,split", [(8, 0), (4104, 512), (32008, 0)])
+def test_accept_nan_elects_nothing(V, split, dtype):
+    """NaN entries are passed over: a row that holds nothing else has no
+    prediction, one of NaN and -inf predicts its first -inf."""
+    x = np.random.default_rng(V).standard_normal((3, 4, V)).astype(np.float32)
+    x[0, 0] = np.nan
+    x[0, 1, : V // 2 + 1] = np.nan
+    x[0, 2] = np.nan
+    x[0, 2, V - 2:] = -np.inf
+    x[1, :, ::2] = np.nan
+    x[2] = -np.inf
+    x[2, 1, : V // 2] = np.nan
+    x[2, 2, V - 1] = -1e30
+    if dtype == "bf16":
+        logits = np.where(np.isnan(x), np.uint16(0x7fc0), wl.f32_to_bf16_bits(x))
+        seen = (logits.astype(np.uint32) << 16).view(np.float32)
+    else:
+        logits = seen = x
+    want = np.array([[np.nonzero(r == np.nanmax(r))[0][0] if not np.isnan(r).all() else -1 for r in b] for b in seen])
+    note(f"case nan V={V} {dtype}")
+    got = run_accept(logits, np.zeros((3, 4), np.int32), np.zeros(3, np.int32), np.full(3, 4, np.int32), dtype, split)
+    assert np.array_equal(got["argmax"], want), (got["argmax"], want)
