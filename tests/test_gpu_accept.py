@@ -303,3 +303,29 @@ def test_accept_nan_elects_nothing(V, split, dtype):
     note(f"case nan V={V} {dtype}")
     got = run_accept(logits, np.zeros((3, 4), np.int32), np.zeros(3, np.int32), np.full(3, 4, np.int32), dtype, split)
     assert np.array_equal(got["argmax"], want), (got["argmax"], want)
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("f16", 128), ("f32", 64), ("f32", 128)])
+def test_compact_path_lengths(dtype, D):
+    """Paths of every number of 256-chunk passes: empty, in place, one node,
+    one that fills a pass, one row more, all 64 shifted, rows past S_max."""
+    d = dev()
+    per = 256 * 16 // (D * (4 if dtype == "f32" else 2))   # rows of one pass
+    ones = lambda n: (1 << n) - 1                          # noqa: E731
+    paths = [0, 1, ones(9), ones(64), 2, 1 << 63, 1 | 4, ones(min(per, 63)) << 1, ones(min(per + 1, 63)) << 1,
+             ones(64) & ~2, 0xAAAAAAAAAAAAAAAA, ones(63) << 1]
+    B, Hkv, S = len(paths), 2, 96
+    ctx = np.array([5, 0, 7, 31, 3, 20, 0, 32, 11, 30, 17, 60], np.int32)   # (the last one's rows pass S)
+    kv = np.random.default_rng(D).standard_normal((2, B, Hkv, S, D)).astype(np.float32)
+    t = torch.from_numpy(kv).to({"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype])
+    want = t.clone()
+    for b, w in enumerate(paths):
+        nodes = [n for n in range(64) if w >> n & 1]
+        for j, n in enumerate(nodes):
+            if ctx[b] + n < S:
+                want[:, b, :, ctx[b] + j] = t[:, b, :, ctx[b] + n]
+    k, v = t[0].to(d), t[1].to(d)
+    note(f"case path lengths {dtype} D={D}")
+    pkg.compact_accepted_kv(k, v, i32(ctx), torch.from_numpy(np.array(paths, np.uint64).view(np.int64)).to(d))
+    torch.cuda.synchronize()
+    assert torch.equal(k.cpu(), want[0]) and torch.equal(v.cpu(), want[1])
