@@ -45,6 +45,7 @@ constexpr int kItemBytes = 8192;           // default item: 8 KB of logits
 // is compared (B = 64, 20 MB: 8.8 us against 9.1 with 8).
 constexpr int kLongBatch = 8, kShortBatch = 4;
 constexpr int kSplitUnit = 512;            // item granularity (entries)
+constexpr int kModeIeee = 1 | (9 << 6);    // s_setreg operand: bit 9 of the MODE register
 constexpr int kMaxChunk = 1024;            // C_max limit
 constexpr int kMaxSeqs = 65536;            // B limit (fixed counter region)
 constexpr int kGroupSeqs = 16;             // sequences a workgroup counts through LDS
@@ -121,6 +122,11 @@ __global__ __launch_bounds__(kThreads, kGroupsPerCU) void accept_kernel(Params p
   __shared__ int group_cnt[kGroupSeqs];
   const int lane = threadIdx.x & 63;
   const int wave = uniform(blockIdx.x * kWavesPerGroup + (threadIdx.x >> 6));
+  // MODE.IEEE off: a maximum with one NaN operand, signalling or quiet, is the
+  // other operand.  (With it on, v_max3_f32 turns a signalling NaN into a quiet
+  // one and the next maximum drops it with all that was accumulated before;
+  // quieting every entry would cost an instruction per entry.)
+  __builtin_amdgcn_s_setreg(kModeIeee, 0);
   const int CS = p.C_max * p.S;            // items per sequence
   const int gq = kWavesPerGroup * p.q;     // items per workgroup range
   const int g0 = blockIdx.x * gq;

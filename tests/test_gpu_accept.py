@@ -329,3 +329,28 @@ def test_compact_path_lengths(dtype, D):
     pkg.compact_accepted_kv(k, v, i32(ctx), torch.from_numpy(np.array(paths, np.uint64).view(np.int64)).to(d))
     torch.cuda.synchronize()
     assert torch.equal(k.cpu(), want[0]) and torch.equal(v.cpu(), want[1])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [8, 4104])
+def test_accept_signalling_nans(V, dtype):
+    """Signalling NaNs, of both signs, are passed over like quiet ones, and
+    hide no entry beside them: in each 16-byte vector the winner stands at
+    every position with NaNs at a varying set of the others."""
+    rng = np.random.default_rng(V)
+    per = 8 if dtype == "bf16" else 4
+    B, C = 16, per
+    x = rng.standard_normal((B, C, V)).astype(np.float32)
+    won = np.arange(C) + per * rng.integers(0, V // per, size=(B, C))   # position k of some vector
+    np.put_along_axis(x, won[..., None], 9.0, 2)
+    x = (wl.f32_to_bf16_bits(x).astype(np.uint32) << 16).view(np.float32)
+    nan = rng.random(x.shape) < 0.5
+    np.put_along_axis(nan, won[..., None], False, 2)
+    nan[0, 0] = True                                # a row of nothing else
+    want = np.where(nan.all(2), -1, won)
+    bits = np.where(rng.random(x.shape) < 0.5, np.uint32(0x7f810000), np.uint32(0xffa00000))   # bit 22 clear: signalling
+    raw = np.where(nan, bits, x.view(np.uint32))
+    logits = (raw >> 16).astype(np.uint16) if dtype == "bf16" else raw.view(np.float32)
+    note(f"case signalling NaNs V={V} {dtype}")
+    got = run_accept(logits, np.zeros((B, C), np.int32), np.zeros(B, np.int32), np.full(B, C, np.int32), dtype)
+    assert np.array_equal(got["argmax"], want), np.argwhere(got["argmax"] != want)[:5]
