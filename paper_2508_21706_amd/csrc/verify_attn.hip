@@ -810,14 +810,14 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
   // of its own row, and within a partial tile the lanes past its last row
   // re-read that row.  K loads that would start past the last row are not
   // issued: those slots keep whatever an earlier tile or merge left there,
-  // and the consumers mask the keys.  A masked key has probability 0 but
-  // must meet finite V values: the first tile of each stage loads every V
-  // slot (LDS starts undefined), later tiles skip the V loads past the last
-  // row too, whose slots then hold rows of an earlier tile (the key-split
-  // merge's scratch stays in the K half).  Paged caches load every V slot
-  // (skipping measured slower there: 77.2 -> 79.5 us on B = 64 with 16-token
-  // pages, against 68.2 -> 67.2 us with a contiguous cache).  The two waves of a producer pair
-  // issue the K and V instructions of even and odd index.
+  // and the consumers mask the keys.  A masked key has probability 0 but is
+  // multiplied by the V row in its slot, which must not come from another
+  // sequence (0 x Inf): V is loaded up to the end of the last row's 16-key
+  // block, and consumers read no block past that one.  Paged caches load
+  // every V slot (skipping measured slower there: 77.2 -> 79.5 us on B = 64
+  // with 16-token pages, against 68.2 -> 67.2 us with a contiguous cache).
+  // The two waves of a producer pair issue the K and V instructions of even
+  // and odd index.
   // (paged) the pool pages of the tile of cu, one per lane of a producer
   // wave: lane l holds the page of the tile's l-th page (at most 33 of them:
   // pages hold at least 8 tokens, tiles at most 256), as the index of its rows
@@ -842,7 +842,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
   // Stage of the wave's pair: the first tile goes to waves 2 and 3, as wave 0
   // comes late from the schedule.
   const int grp = wave < 2 ? 1 : 0;
-  auto dma = [&](const Cursor& cu, int st, int pg, bool all_v) {
+  auto dma = [&](const Cursor& cu, int st, int pg) {
     const int T = seq_T(cu.s);
     const int hi = T - (seq_tiles<C>(cu.s) - 1 - cu.j) * C::kTileKeys;
     const int lo = hi > C::kTileKeys ? hi - C::kTileKeys : 0;
@@ -857,7 +857,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     // row is past the tile's keys is skipped: those scores are masked whatever
     // the slots hold.
     const int n_k = ((last + 1) * C::kSlotsK + 63) / 64;
-    const int n_v = PAGED || all_v ? C::kInstV : ((last + 1) * C::kSlotsV + 63) / 64;
+    const int n_v = PAGED ? C::kInstV : ((last / kBlk + 1) * kBlk * C::kSlotsV + 63) / 64;
     // the k-th load of this wave: LDS slots sl of each half, the row that each
     // belongs to and its 16 bytes there (a pad slot re-reads its row's last
     // chunk)
@@ -942,7 +942,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     for (; v < count; v += 2) {
       if (v >= 2) gave_up |= !wait_count(&empty_cnt[grp], kConsumers * (v >> 1), p.spin_limit);
       if (v == 1) gave_up |= !wait_count(&full_cnt[0], 2, p.spin_limit);
-      dma(cu, grp, pg, v < 2);
+      dma(cu, grp, pg);
       if constexpr (PAGED) {
         // the next tile's table entries ride the wait for this tile's loads
         if (v + 2 < count) {
@@ -1230,15 +1230,15 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       // Key blocks kb0 and kb1 = kb0 + nks of the tile form a pair: two
       // independent score chains, one softmax step over their 8 keys per
       // lane, and (bf16) one 32-key P V contraction per d block.  A block
-      // past the tile's keys reads staged rows that hold finite data and
-      // is masked like any key >= hi.
+      // kb1 past the tile's keys is masked like any key >= hi; its K rows may
+      // be stale, and V is not read there (f32) or read in block kb0.
       // (an inactive wave runs no pair)
       for (int kb0 = active ? kslot : C::kNKB; kb0 < C::kNKB; kb0 += 2 * nks) {
         if (kb0 * kBlk >= nk) break;
         const int key0 = lo + kb0 * kBlk;
         const int key1 = key0 + nks * kBlk;
-        const int bstride = nks * kBlk * C::kPitchK;    // LDS bytes from block kb0 to kb1 (K)
-        const int vbstride = nks * kBlk * C::kPitchV;   // (V)
+        const int bstride = nks * kBlk * C::kPitchK;   // LDS bytes from block kb0 to kb1 (K)
+        const bool kb1_in = (kb0 + nks) * kBlk < nk;
         // S^T = K Q^T for 16 keys x 16 rows per block; lane (row lm,
         // quarter lg) gets the keys key + 4 lg + r, r = 0..3
         const char* krow = ks + (kb0 * kBlk + lm) * C::kPitchK + 16 * lg;
@@ -1293,6 +1293,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
         // key + 4 lg + t / 4, columns 16 db + 4 (t % 4) .. + 3.
         i16x4 vt[W16 ? 2 * C::kDB : 1];
         if constexpr (W16) {
+          const int vbstride = kb1_in ? nks * kBlk * C::kPitchV : 0;   // LDS bytes from block kb0 to kb1 (V)
           typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
           const char* vrow = vs + (kb0 * kBlk + 4 * lg + (lm >> 2)) * C::kPitchV + 8 * (lm & 3);
 #pragma unroll
@@ -1372,7 +1373,8 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
           // f32: lane (lm, lg) takes V rows key + 4 lg + r at d = 16 db + lm
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
-            const char* vrow = vs + (kb0 * kBlk + 4 * lg) * C::kPitchV + h * vbstride + 4 * lm;
+            if (h == 1 && !kb1_in) break;
+            const char* vrow = vs + ((kb0 + h * nks) * kBlk + 4 * lg) * C::kPitchV + 4 * lm;
 #pragma unroll
             for (int db = 0; db < C::kDB; ++db)
 #pragma unroll
