@@ -498,7 +498,7 @@ __device__ __forceinline__ void merge_units(const Params& p, const uint32_t* seq
         }
       }
       // one rescaling per batch, and one weight per piece (a piece in which
-      // the row sees no key, or none at all, weighs 0)
+      // the row sees no key, all 0, or none at all weighs 0)
 #pragma unroll
       for (int it = 0; it < kItems; ++it) {
         float nm = m[it];
@@ -1170,9 +1170,10 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
         const int r = idx / (D / 4);
         const int d4 = idx - r * (D / 4);
         const float l = po[rows * D + 2 * r + 1];
-        __builtin_amdgcn_raw_buffer_store_b128(
-            __builtin_bit_cast(i32x4, *reinterpret_cast<const f32x4*>(po + r * D + 4 * d4) * (l > 0.f ? 1.f / l : 0.f)),
-            ws_o_rsrc, ((row0 + r) * D + 4 * d4) * 4, 0, kDeviceCoherent);
+        f32x4 x = *reinterpret_cast<const f32x4*>(po + r * D + 4 * d4) * (l > 0.f ? 1.f / l : 0.f);
+        if (l == 0.f) x = f32x4{0.f, 0.f, 0.f, 0.f};   // no key of the piece is visible
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, x), ws_o_rsrc, ((row0 + r) * D + 4 * d4) * 4, 0,
+                                               kDeviceCoherent);
       }
       for (int r = ctid; r < rows; r += kCThreads) {
         const float m = po[rows * D + 2 * r], l = po[rows * D + 2 * r + 1];
@@ -1523,6 +1524,13 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       pend = true;
       pend_whole = whole;
       pend_ok = active && row_valid;
+      // a piece of which a row sees no key leaves that row 0 (at lse -inf),
+      // whatever V holds there: the merge weighs it 0, and 0 x Inf is NaN
+      if (!whole && __any(pend_ok && fl == 0.f)) {
+#pragma unroll
+        for (int u = 0; u < C::kDB; ++u)
+          if (fl == 0.f) o[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
       pend_inv = fl > 0.f ? 1.f / fl : 0.f;
       pend_lse = fl > 0.f ? (fm + log2f(fl)) * kLn2 : -INFINITY;
       pend_row = whole ? (b * p.C_max + tok) * p.Hq + kvh * g + row - tok * g

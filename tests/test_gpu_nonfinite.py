@@ -32,3 +32,20 @@ def test_sequences_do_not_reach_each_other(C, dtype, D):
         note(f"case C={C} {dtype} D={D} grid_blocks={grid}")
         o, s = run_gpu(inp, dtype, grid)
         compare(o[ok], s[ok], ref_o[ok], ref_l[ok], dtype, f"grid={grid}")
+
+
+def test_piece_without_visible_keys():
+    """A unit's last tile holds draft tokens only: rows before them see no key
+    of it.  As a piece of its own it weighs nothing there, whatever the values
+    of its tokens are.  (64-key tiles; with ranges of two tiles, units of seven
+    and three tiles leave the last one alone.)"""
+    C, ctx = 100, [7 * 64 - 100, 3 * 64 - 100, 7 * 64 - 100]
+    inp = _custom(3, 1, 1, 128, "f32", ctx, [C] * 3, C)
+    ref_o, ref_l = verify_attn_ref(inp["q"], inp["k_cache"], inp["v_cache"], inp["ctx_lens"], inp["chunk_lens"],
+                                   inp["scale"], "f32")
+    for b, l in enumerate(ctx):
+        inp["v_cache"][b, :, l + C - 8:l + C] = np.inf
+    rows = C - 64   # of every sequence: no key of the last tile is visible
+    note("case last tile invisible")
+    o, s = run_gpu(inp, "f32", 0)
+    compare(o[:, :rows], s[:, :rows], ref_o[:, :rows], ref_l[:, :rows], "f32", "last tile invisible")
