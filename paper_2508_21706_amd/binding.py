@@ -411,7 +411,7 @@ def accept_greedy_tree(logits: torch.Tensor, tokens: torch.Tensor, draft_mask: t
     if out is None:
         out = {}
     if "path" not in out:
-        out["path"] = torch.empty((B,), dtype=torch.int64, device=logits.device)
+        out["path"] = _empty((B,), torch.int64, logits.device, stream)
     _check(out["path"], "path", (B,), torch.int64)
     return accept_greedy(logits, tokens, ctx_lens, chunk_lens, out=out, workspace=workspace, split=split,
                          stream=stream, in_place=in_place, _tree=(draft_mask, out["path"]))
@@ -444,7 +444,8 @@ def accept_greedy(logits: torch.Tensor, tokens: torch.Tensor, ctx_lens: torch.Te
     chunk_lens int32 [B], all on the GPU.  Returns a dict of int32 tensors:
     argmax [B, C_max], accepted [B], next_token [B], new_ctx_lens [B] (with
     ``in_place``, ctx_lens itself is updated and returned as new_ctx_lens).
-    ``out`` may supply those tensors.
+    ``out`` may supply those tensors; missing ones come from the launch
+    stream's pool, as in ``verify_attn``.
     """
     lib = load_library()
     if logits.dim() != 3:
@@ -459,7 +460,7 @@ def accept_greedy(logits: torch.Tensor, tokens: torch.Tensor, ctx_lens: torch.Te
         out = {}
     for key in ("argmax", "accepted", "next_token", "new_ctx_lens"):
         if key not in out and not (in_place and key == "new_ctx_lens"):
-            out[key] = torch.empty((B, C_max) if key == "argmax" else (B,), dtype=torch.int32, device=dev)
+            out[key] = _empty((B, C_max) if key == "argmax" else (B,), torch.int32, dev, stream)
     if in_place:
         out["new_ctx_lens"] = ctx_lens
     _check(out["argmax"], "argmax", (B, C_max), torch.int32)

@@ -354,3 +354,30 @@ def test_accept_signalling_nans(V, dtype):
     note(f"case signalling NaNs V={V} {dtype}")
     got = run_accept(logits, np.zeros((B, C), np.int32), np.zeros(B, np.int32), np.full(B, C, np.int32), dtype)
     assert np.array_equal(got["argmax"], want), np.argwhere(got["argmax"] != want)[:5]
+
+
+@pytest.mark.parametrize("tree", [False, True])
+def test_accept_side_stream_without_buffers(tree):
+    """A call on a non-current stream without ``out`` or a workspace takes
+    both from that stream's pool: blocks that the current stream has freed,
+    but has yet to write, are not among them."""
+    from oracle import accept_tree_ref
+    d = dev()
+    inp, tokens, words, chunk = _tree_case(86, 8, 16, 32000, "bf16")
+    ref = (accept_tree_ref(inp["logits"], tokens, words, inp["ctx_lens"], chunk, "bf16") if tree
+           else accept_greedy_ref(inp["logits"], tokens, inp["ctx_lens"], chunk, "bf16"))
+    x, t, l, c = logits_dev(inp["logits"], "bf16"), i32(tokens), i32(inp["ctx_lens"]), i32(chunk)
+    mask = torch.from_numpy(words.view(np.int64)).to(d)
+    side = torch.cuda.Stream(device=d)
+    torch.cuda.synchronize()
+    for trial in range(3):
+        note(f"case side stream, no buffers, tree={tree} trial {trial}")
+        torch.cuda._sleep(4_000_000)   # a few milliseconds of the current stream
+        junk = [torch.full((n,), 7, dtype=torch.int32, device=d) for n in (8, 16, 8 * 16) for _ in range(16)]
+        del junk
+        out = (pkg.accept_greedy_tree(x, t, mask, l, c, stream=side) if tree
+               else pkg.accept_greedy(x, t, l, c, stream=side))
+        torch.cuda.synchronize()
+        assert set(out) == set(ref)
+        for k in ref:
+            assert np.array_equal(out[k].cpu().numpy().astype(np.int64), np.asarray(ref[k]).astype(np.int64)), k
