@@ -64,6 +64,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "schedule.h"
 #include "specmoe_verify.h"
 
 // Device scratch of specmoe_verify_attn_noalloc (for callers that cannot
@@ -77,6 +78,10 @@ static __device__ __attribute__((aligned(256))) char scratch[kScratchBytes];
 
 namespace {
 
+using sched::kBlk;
+using sched::seq_c;
+using sched::seq_T;
+
 constexpr int kProducers = 4;                 // waves that stream K/V into LDS
 constexpr int kConsumers = 8;                 // waves that compute
 constexpr int kWaves = kProducers + kConsumers;
@@ -84,7 +89,6 @@ constexpr int kThreads = 64 * kWaves;
 constexpr int kCThreads = 64 * kConsumers;
 constexpr int kStages = 2;                    // LDS stages: one per producer pair
 constexpr int kHalf = 32768;                  // K bytes (and V bytes) of one tile
-constexpr int kBlk = 16;                      // keys (and query rows) per MFMA block
 constexpr int kMaxRows = 128;                 // row blocks per unit <= 8
 constexpr int kDefaultGrid = 256;             // persistent workgroups: one per CU of an MI355X
 constexpr int kMaxGrid = 2048;
@@ -139,7 +143,7 @@ struct Params {
   int Rcap;         // C_max * g
   int P;            // persistent workgroups
   float sl2;        // scale * log2(e)
-  int flat;         // the schedule counts tiles, not their costs (totals past 32 bits)
+  int flat;         // sched::Launch::flat
   const uint64_t* draft_mask;   // [B][C_max] draft-mask words (tree drafts only)
   // paged caches only: k and v are [num_pages][Hkv][1 << page_shift][D]
   const int32_t* block_table;   // [B][pages_per_seq]
@@ -304,96 +308,13 @@ __device__ __forceinline__ uint32_t load_seq(const Params& p, int b) {
   if (l > p.S_max - c) l = p.S_max - c;
   return ((uint32_t)(l + c) << 8) | (uint32_t)c;
 }
-__device__ __forceinline__ int seq_T(uint32_t s) { return (int)(s >> 8); }
 // a value every lane of the wave holds, moved to a scalar register
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
-__device__ __forceinline__ int seq_c(uint32_t s) { return (int)(s & 0xffu); }
 template <class C>
 __device__ __forceinline__ int seq_tiles(uint32_t s) {
-  return seq_c(s) == 0 ? 0 : (seq_T(s) + C::kTileKeys - 1) / C::kTileKeys;
+  return sched::seq_tiles(s, C::kTileKeys);
 }
-
-// Cost of one tile of a sequence with c chunk tokens: a fixed part for
-// streaming the tile, plus one per 16-row block of the unit's c * g query
-// rows.  A unit with many rows can take longer on a tile than the tile's
-// HBM stream lasts, so workgroups get equal cost rather than equal tiles.
-// The weights follow measured tile times (ragged chunks, 1-7 row blocks:
-// 2.7, 3.1 and 3.3 us per tile for 1-2, 3-4 and 5-7 blocks).
-constexpr int kTileCost = 10;
-__device__ __forceinline__ int tile_cost(const Params& p, uint32_t s, int whole) {
-  return whole || p.flat ? 1 : kTileCost + (seq_c(s) * p.g + kBlk - 1) / kBlk;
-}
-// Extra costs of a unit: at its start (a first tile that is mostly partial,
-// the switch of Q) and at its end (the result's stores and, for units of one
-// or two row blocks, the merge of the key-split states; charged after its
-// last tile), so ranges that cross more unit boundaries get fewer tiles.  A
-// range that starts inside a unit pays for that unit's end.  (Measured: on
-// B = 64 with chunks of 5 and 4 query heads per KV head a unit end holds a
-// workgroup ~1.6 us and its start ~0.6 us, against ~2.2 us per tile; a fit
-// over eight splits of the tree workload, four row blocks per unit, gives
-// 2.2 us per unit and 2.3 per tile: with 3 + 6 for it, not 6 + 0, 77.9 -> 77.0
-// us per call, ragged chunks 123.1 -> 122.5.)
-constexpr int kStartSplit = 3, kEndSplit = 9;   // units of one or two row blocks
-constexpr int kStartRest = 3, kEndRest = 6;     // larger units
-constexpr int kExtraMax = kStartSplit + kEndSplit > kStartRest + kEndRest ? kStartSplit + kEndSplit : kStartRest + kEndRest;
-__device__ __forceinline__ bool split_unit(const Params& p, uint32_t s) { return seq_c(s) * p.g <= 2 * kBlk; }
-__device__ __forceinline__ int start_cost(const Params& p, uint32_t s, int whole) {
-  return whole || p.flat ? 0 : split_unit(p, s) ? kStartSplit : kStartRest;
-}
-__device__ __forceinline__ int end_cost(const Params& p, uint32_t s) {
-  return p.flat ? 0 : split_unit(p, s) ? kEndSplit : kEndRest;
-}
-// Launches of few units (at most half the workgroups, one sequence per lane of
-// the scheduling wave): ranges are cut inside units only, `whole` tiles each,
-// so that no workgroup ends two units or holds two pieces: a second unit in a
-// range costs its end (1.2 us), and often the publication and merge of a
-// second piece, as much as one or two tiles of a launch that has two to
-// twenty per workgroup.  `whole` is the smallest that leaves at most one range
-// per workgroup, of kWholeTries from the even share on (past those the uneven
-// last ranges of units waste more), but at least kWholeMin (ranges of one tile
-// pay more for their merge than they save), and kWholeUnit where that makes
-// units whole on average.  Against equal cost: 8 KV heads, B = 1 with 300
-// tokens 12.4 -> 10.5 us, B = 8 with 512-2048 21.9 -> 19.4, B = 16 with 300-900
-// 20.8 -> 18.2, B = 2 with 16k 33.7 -> 31.0, B = 4 with 20-30k 72.3 -> 71.2;
-// B = 4 with 512-2048 (two tiles per range either way) 15.5 -> 15.6.
-constexpr int kWholeUnit = 3, kWholeMin = 2, kWholeTries = 4;
-// cost of one unit (one KV head) of a sequence with packed lengths s: its n
-// tiles, its start and its end; with `whole`, its tiles rounded up to whole
-// ranges
-__device__ __forceinline__ int unit_cost(const Params& p, int n, uint32_t s, int whole) {
-  if (whole) return (n + whole - 1) / whole * whole;
-  return n > 0 ? n * tile_cost(p, s, 0) + start_cost(p, s, 0) + end_cost(p, s) : 0;
-}
-
-// Tile schedule shared by every workgroup of a launch.  The tiles of all
-// units form one list [0, N) in (sequence, KV head, tile) order; tile j of
-// unit kvh of sequence b starts at cost Hkv cpref[b] + kvh U_b + (j > 0 ?
-// S_b + j w_b : 0), w_b its sequence's tile cost, S_b and E_b its unit-start
-// and unit-end costs and U_b = n_b w_b + S_b + E_b a unit's cost, out of Wt
-// in all.  The costs [0, Wt) are cut into Pe ranges, the first Wt mod Pe of
-// them one longer than the rest (width); range q holds the tiles whose start
-// cost lies in it.  With Pe <= Wt / max_b (w_b + S_b + E_b) no range is
-// empty, since consecutive tile starts are at most max_b (w_b + S_b + E_b)
-// apart.  Everything fits 32 bits: a launch whose total cost could reach 2^31
-// counts tiles instead (Params::flat), fewer than 2^30 (host check).  The
-// search sits ahead of every workgroup's first load, and the list of shared
-// units ahead of its first tile's compute: with 64-bit costs and
-// double-precision quotients the first took 1.5 us and a call on two
-// sequences began to compute 6.0 us into the launch; in 32 bits 0.8 us and
-// 4.0 us (B = 4, 24 MB of K and V: 19.3 -> 17.5 us per call; B = 64, 347 MB:
-// 63.8 -> 63.2 us, as the stream makes up for most of it).
-struct Sched {
-  int N, Pe, whole;
-  uint32_t Wt, width, longer;
-  __device__ uint32_t bound(int q) const { return (uint32_t)q * width + min((uint32_t)q, longer); }   // range q's first cost
-  // range of the tile that starts at cost c
-  __device__ int owner(uint32_t c) const {
-    const uint32_t cut = longer * (width + 1);
-    const bool low = c < cut;
-    return (int)((low ? c : c - cut) / (low ? width + 1 : width) + (low ? 0 : longer));
-  }
-};
 
 // Position of a tile: sequence, KV head, tile index inside the unit, and the
 // sequence's packed lengths.
@@ -608,7 +529,8 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
   // contiguous sequences [l per, (l + 1) per).  Every range is streamed in
   // order.
   __shared__ __attribute__((aligned(16))) i32x4 sh_sched[4];
-  Sched sc;
+  const sched::Launch launch = {g, Hkv, p.C_max, p.P, p.flat};
+  sched::Sched sc;
   if (wave == 0) {
     const int per = (B + 63) / 64;
     const int b_lo = min(lane * per, B);
@@ -618,7 +540,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     auto add = [&](uint32_t s) {     // (s = 0: no tiles, no cost)
       const int n = seq_tiles<C>(s);
       my_tiles += n;
-      my_cost += unit_cost(p, n, s, 0);
+      my_cost += sched::unit_cost(launch, n, s, 0);
     };
     if (per == 1) {
       if (lane < B) {
@@ -641,27 +563,19 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     }
     const int incl = wave_scan(my_tiles);
     const int total = __builtin_amdgcn_readlane(incl, 63);
-    sc.N = total * Hkv;   // tiles of all units (< 2^30, host check)
-    // few units: ranges of `whole` tiles of one unit each, if a small enough
-    // one leaves at most P ranges
+    const int N = total * Hkv;   // tiles of all units (< 2^30, host check)
+    // few units: ranges of `whole` tiles of one unit each
     sc.whole = 0;
     int cincl = 0;
     if (per == 1 && !p.flat) {
       const int units = __builtin_popcountll(__ballot(my_tiles > 0)) * Hkv;
-      if (units > 0 && 2 * units <= p.P) {
-        int t = sc.N <= kWholeUnit * units ? kWholeUnit : kWholeMin;
-        if (sc.N > t * p.P) t = (sc.N + p.P - 1) / p.P;
-        for (int tries = 0; tries < kWholeTries; ++tries, ++t) {
-          const int k = (my_tiles + t - 1) / t;   // ranges per unit
-          const int kincl = wave_scan(k);
-          if (__builtin_amdgcn_readlane(kincl, 63) * Hkv <= p.P) {
-            sc.whole = t;
-            my_cost = k * t;
-            cincl = kincl * t;
-            break;
-          }
-        }
-      }
+      sc.whole = sched::pick_whole(launch, N, units, [&](int t) {
+        const int k = (my_tiles + t - 1) / t;   // ranges per unit
+        const int kincl = wave_scan(k);
+        cincl = kincl * t;
+        return __builtin_amdgcn_readlane(kincl, 63);
+      });
+      if (sc.whole) my_cost = sched::unit_cost(launch, my_tiles, my_s, sc.whole);
     }
     if (!sc.whole) cincl = wave_scan(my_cost);
     // exclusive prefixes: those of sequence b_lo (the totals in lanes without
@@ -675,7 +589,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
         pref[b] = run;
         cpref[b] = crun;
         run += n;
-        crun += unit_cost(p, n, s, sc.whole);
+        crun += sched::unit_cost(launch, n, s, 0);
       }
     }
     if (lane < kStages) {
@@ -687,23 +601,10 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       pub_arrive[lane] = 0;
       sh_flag[lane] = 0;
     }
-    // every tile costs at most w_hi with its unit's start and end, so with at
-    // most Wt / w_hi ranges (and at least one when there are tiles) no range
-    // is empty
-    sc.Wt = (uint32_t)Hkv * (uint32_t)__builtin_amdgcn_readlane(cincl, 63);
-    const uint32_t w_hi = p.flat ? 1 : kTileCost + (p.C_max * g + kBlk - 1) / kBlk + kExtraMax;
-    if (sc.whole) sc.Pe = (int)(sc.Wt / (uint32_t)sc.whole);
-    else sc.Pe = sc.Wt >= (uint32_t)p.P * w_hi ? p.P : sc.N > 0 ? max((int)(sc.Wt / w_hi), 1) : 0;
-    sc.width = sc.Wt / (uint32_t)max(sc.Pe, 1);
-    sc.longer = sc.Wt - sc.width * (uint32_t)sc.Pe;
-    // The sequence whose units hold cost X < Wt: the last one with Hkv
-    // cpref[b] <= X (it has tiles, as the next prefix is past X).
-    struct At {
-      int b, n, t0;       // sequence, tiles per unit, tiles before its units
-      uint32_t s, c0, U;  // packed lengths, cost before its units, cost of a unit
-    };
+    sc.cut(launch, N, __builtin_amdgcn_readlane(cincl, 63));
+    // The last sequence b with Hkv cpref[b] <= X
     auto seq_at = [&](uint32_t X) {
-      At a;
+      sched::At a;
       // (lane 0's prefix 0 always passes, the totals in lanes without
       // sequences never do)
       const int l = 63 - __builtin_clzll(__ballot((uint32_t)cex * (uint32_t)Hkv <= X));
@@ -724,49 +625,24 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       a.n = seq_tiles<C>(a.s);
       a.t0 *= Hkv;
       a.c0 *= (uint32_t)Hkv;
-      a.U = (uint32_t)unit_cost(p, a.n, a.s, sc.whole);
+      a.U = (uint32_t)sched::unit_cost(launch, a.n, a.s, sc.whole);
       return a;
     };
     if (pid < sc.Pe) {
-      // the first tile that starts at or after the range's first cost, ...
-      const uint32_t X = sc.bound(pid);
-      At f = seq_at(X);
-      uint32_t kvh = (X - f.c0) / f.U;
-      uint32_t cf = f.c0 + kvh * f.U;
-      const uint32_t w = (uint32_t)tile_cost(p, f.s, sc.whole), S = (uint32_t)start_cost(p, f.s, sc.whole), r = X - cf;
-      uint32_t j = r == 0 ? 0 : r <= S ? 1 : (r - S + w - 1) / w;
-      // (rounded up to a unit's end: the next unit's first tile)
-      int g0 = f.t0 + (int)kvh * f.n + min((int)j, f.n);
-      if ((int)j >= f.n) {
-        j = 0;
-        cf += f.U;
-        if ((int)++kvh == Hkv) {
-          kvh = 0;
-          f = seq_at(cf);
-        }
-      }
-      // ... and the last one that starts before its end
-      const uint32_t Y = sc.bound(pid + 1) - 1;
-      const At e = seq_at(Y);
-      const uint32_t kvl = (Y - e.c0) / e.U;
-      const uint32_t cl = e.c0 + kvl * e.U;
-      const uint32_t wl = (uint32_t)tile_cost(p, e.s, sc.whole), Sl = (uint32_t)start_cost(p, e.s, sc.whole), rl = Y - cl;
-      const int jl = rl < Sl + wl ? 0 : min((int)((rl - Sl) / wl), e.n - 1);
-      const int g1 = e.t0 + (int)kvl * e.n + jl + 1;
+      const sched::Range r = sched::range_of(launch, sc, pid, seq_at);
       if (lane == 0) {
-        sh_sched[1] = i32x4{g1, f.b, (int)kvh, (int)j};
-        sh_sched[2] = i32x4{(int)f.s, (int)cf, e.b, (int)kvl};
-        sh_sched[3] = i32x4{(int)e.s, (int)cl, g0, sc.whole};
+        sh_sched[1] = i32x4{r.g1, r.first.b, r.kvh, r.j};
+        sh_sched[2] = i32x4{(int)r.first.s, (int)r.cf, r.last.b, r.kvl};
+        sh_sched[3] = i32x4{(int)r.last.s, (int)r.cl, r.g0, sc.whole};
       }
     }
-    if (lane == 0) sh_sched[0] = i32x4{sc.Pe, (int)sc.width, (int)sc.longer, sc.N};
+    if (lane == 0) sh_sched[0] = i32x4{sc.Pe, (int)sc.width, (int)sc.longer, 0};
   }
   __syncthreads();
   const i32x4 sw0 = sh_sched[0], sw1 = sh_sched[1], sw2 = sh_sched[2], sw3 = sh_sched[3];
   sc.Pe = uniform(sw0[0]);
   sc.width = (uint32_t)uniform(sw0[1]);
   sc.longer = (uint32_t)uniform(sw0[2]);
-  sc.N = uniform(sw0[3]);
   if (pid >= sc.Pe) {
     pad_rows(tid, kThreads);
     return;
@@ -837,7 +713,6 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     return r;
   };
   constexpr int kDmaK = (C::kInstK + 1) / 2, kDmaV = (C::kInstV + 1) / 2;   // loads per producer wave and tile
-  constexpr int kDmaMax = kDmaK > kDmaV ? kDmaK : kDmaV;
   const int pw = wave & 1;
   // Stage of the wave's pair: the first tile goes to waves 2 and 3, as wave 0
   // comes late from the schedule.
@@ -1090,7 +965,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       const int n = seq_tiles<C>(s);
       if (lane == 0)
         sh_share[k] = i32x4{k == 0 ? first.b * Hkv + first.kvh : uniform(sw2[2]) * Hkv + uniform(sw2[3]), sc.owner(c),
-                            sc.owner(n > 1 ? c + start_cost(p, s, sc.whole) + (n - 1) * tile_cost(p, s, sc.whole) : c), 0};
+                            sc.last_owner(launch, s, n, c), 0};
     }
   }
 #pragma unroll
@@ -1746,8 +1621,8 @@ int validate_desc(const specmoe_verify_desc* d) {
   const int64_t tile = key_tile(d->dtype, d->D);
   if ((int64_t)kMaxSeqs * d->Hkv * ((d->S_max + tile - 1) / tile) >= ((int64_t)1 << 30)) return SPECMOE_ERR_SHAPE;
   // the per-KV-head tile cost prefix of the schedule fits in 32 bits
-  const int64_t w_hi = kTileCost + (d->C_max * g + kBlk - 1) / kBlk + kExtraMax;
-  if ((int64_t)kMaxSeqs * ((d->S_max + tile - 1) / tile) * w_hi >= ((int64_t)1 << 31)) return SPECMOE_ERR_SHAPE;
+  const int64_t most = sched::most_cost({(int)g, d->Hkv, d->C_max, 0, 0});
+  if ((int64_t)kMaxSeqs * ((d->S_max + tile - 1) / tile) * most >= ((int64_t)1 << 31)) return SPECMOE_ERR_SHAPE;
   return SPECMOE_OK;
 }
 
@@ -1910,12 +1785,8 @@ int run(const void* q, const void* k_cache, const void* v_cache, const int32_t* 
   p.Rcap = pl.Rcap;
   p.P = pl.P;
   p.sl2 = scale * kLog2e;
-  // the most a launch's tiles can cost (every sequence S_max long); past 31
-  // bits the schedule counts tiles, of which validate_desc allows fewer than
-  // 2^30
-  const int64_t tiles = (desc->S_max + key_tile(desc->dtype, desc->D) - 1) / key_tile(desc->dtype, desc->D);
-  const int64_t unit = tiles * (kTileCost + (pl.Rcap + kBlk - 1) / kBlk) + kExtraMax;
-  p.flat = (int64_t)(desc->B < kMaxSeqs ? desc->B : kMaxSeqs) * desc->Hkv * unit >= ((int64_t)1 << 31);
+  const int tiles = (desc->S_max + key_tile(desc->dtype, desc->D) - 1) / key_tile(desc->dtype, desc->D);
+  p.flat = sched::counts_tiles({pl.g, desc->Hkv, desc->C_max, pl.P, 0}, desc->B < kMaxSeqs ? desc->B : kMaxSeqs, tiles);
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();  // clear a stale error from unrelated work

@@ -1,6 +1,7 @@
 """GPU parity where the tile schedule changes its form: batches of one and of
 several sequences per lane with runs of empty ones, and launches whose total
-cost could pass 31 bits, which are split by tile counts."""
+cost could pass 31 bits, which are split by tile counts.  (The split itself, up
+to the largest totals, is checked on the CPU in test_schedule.py.)"""
 import numpy as np
 import pytest
 import torch
@@ -26,9 +27,11 @@ def test_sequences_per_lane(B):
 
 @pytest.mark.parametrize("B", [188, 190])
 def test_total_cost_at_31_bits(B):
-    """16 KV heads of 64768 tiles of 256 keys, at least 11 cost units each:
-    B = 188 stays below 2^31, B = 190 passes it.  All sequences share one page
-    of 65536 tokens, so their lengths may be short and the cache small."""
+    """The kernel on both sides of the host's choice of the schedule's form: 16
+    KV heads of up to 64768 tiles of 256 keys, at least 11 cost units each, stay
+    below 2^31 with B = 188 and could pass it with B = 190.  The lengths are
+    short (all sequences share one page of 65536 tokens), so this runs the
+    form that counts tiles, not the totals that call for it."""
     d = dev()
     Hq = Hkv = 16
     D, C, ps, pages = 64, 2, 65536, 253
