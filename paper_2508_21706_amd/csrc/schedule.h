@@ -68,6 +68,14 @@ SCHED_FN int counts_tiles(const Launch& p, int B, int tiles) {
   const int64_t unit = (int64_t)tiles * (kTileCost + (p.C_max * p.g + kBlk - 1) / kBlk) + kExtraMax;
   return (int64_t)B * p.Hkv * unit >= ((int64_t)1 << 31);
 }
+// cost of one unit (one KV head) of a sequence with packed lengths s: its n
+// tiles, its start and its end; with `whole`, its tiles rounded up to whole
+// ranges
+SCHED_FN int unit_cost(const Launch& p, int n, uint32_t s, int whole) {
+  if (whole) return (n + whole - 1) / whole * whole;
+  return n > 0 ? n * tile_cost(p, s, 0) + start_cost(p, s, 0) + end_cost(p, s) : 0;
+}
+
 // Launches of few units (at most half the workgroups, one sequence per lane of
 // the scheduling wave): ranges are cut inside units only, `whole` tiles each,
 // so that no workgroup ends two units or holds two pieces: a second unit in a
@@ -81,23 +89,43 @@ SCHED_FN int counts_tiles(const Launch& p, int B, int tiles) {
 // tokens 12.4 -> 10.5 us, B = 8 with 512-2048 21.9 -> 19.4, B = 16 with 300-900
 // 20.8 -> 18.2, B = 2 with 16k 33.7 -> 31.0, B = 4 with 20-30k 72.3 -> 71.2;
 // B = 4 with 512-2048 (two tiles per range either way) 15.5 -> 15.6.
-// N tiles and `units` units in all; ranges(t): ranges of t tiles per KV head.
-constexpr int kWholeUnit = 3, kWholeMin = 2, kWholeTries = 4;
-template <class RANGES>
-SCHED_FN int pick_whole(const Launch& p, int N, int units, RANGES ranges) {
+//
+// Ranges of a fixed number of tiles are uneven where units differ in rows or
+// leave short last ranges, and the launch ends with the longest.  Where that
+// one costs over kWholeUneven half tiles more than the average range, cost is
+// cut equally after all (4 KV heads of 7 query heads, chunks of 1-16, B = 28
+// with 1-10k tokens: 74.9 us in ranges of 21 tiles, 67.8 at equal cost; 2 KV
+// heads, fp32, B = 56 with 128-3000: 53.7 and 48.5).  Fewer ranges than
+// workgroups, if even, stream as fast: 8 KV heads, B = 12 with 3800 tokens,
+// 192 ranges of 15 tiles 39.1 us, at equal cost 41.0.  Over 500 launches timed
+// both ways, the form chosen takes 0.4% longer than the better one of each with
+// 6 or 7 half tiles, 0.8% with 4, 0.5% with 8 and 0.8% without a limit.  Not
+// asked of ranges of up to kWholeShort tiles: such launches would notice the
+// two reductions (0.1 us), and none of the 500 is uneven enough.
+//
+// N tiles and `units` units in all.  ranges(t): ranges of t tiles per KV head;
+// excess(t): the most, over the sequences, of range_excess; cost(): of one KV
+// head's units.
+constexpr int kWholeUnit = 3, kWholeMin = 2, kWholeTries = 4, kWholeUneven = 7, kWholeShort = 4;
+// twice the cost of a sequence's longest range of t tiles, less kWholeUneven of
+// its half tiles
+SCHED_FN int range_excess(const Launch& p, int n, uint32_t s, int t) {
+  if (n == 0) return 0;
+  return (2 * (n < t ? n : t) - kWholeUneven) * tile_cost(p, s, 0) + 2 * (start_cost(p, s, 0) + end_cost(p, s));
+}
+template <class RANGES, class EXCESS, class COST>
+SCHED_FN int pick_whole(const Launch& p, int N, int units, RANGES ranges, EXCESS excess, COST cost) {
   if (units == 0 || 2 * units > p.P) return 0;
   int t = N <= kWholeUnit * units ? kWholeUnit : kWholeMin;
   if (N > t * p.P) t = (N + p.P - 1) / p.P;
-  for (int tries = 0; tries < kWholeTries; ++tries, ++t)
-    if (ranges(t) * p.Hkv <= p.P) return t;
+  for (int tries = 0; tries < kWholeTries; ++tries, ++t) {
+    const int k = ranges(t);
+    if (k * p.Hkv <= p.P) {
+      if (__builtin_expect(t > kWholeShort, 0) && (int64_t)excess(t) * k > 2 * (int64_t)cost()) return 0;
+      return t;
+    }
+  }
   return 0;
-}
-// cost of one unit (one KV head) of a sequence with packed lengths s: its n
-// tiles, its start and its end; with `whole`, its tiles rounded up to whole
-// ranges
-SCHED_FN int unit_cost(const Launch& p, int n, uint32_t s, int whole) {
-  if (whole) return (n + whole - 1) / whole * whole;
-  return n > 0 ? n * tile_cost(p, s, 0) + start_cost(p, s, 0) + end_cost(p, s) : 0;
 }
 
 // Tile schedule shared by every workgroup of a launch.  The tiles of all

@@ -260,6 +260,17 @@ __device__ __forceinline__ int wave_scan(int x) {
   return x;
 }
 
+// Most of 0 and the 64 lanes' values, the same way.
+__device__ __forceinline__ int wave_most(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
 // Two floats rounded (to nearest even) to bf16 and packed, lo in the low
 // half: one v_cvt_pk_bf16_f32.
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -569,12 +580,15 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     int cincl = 0;
     if (per == 1 && !p.flat) {
       const int units = __builtin_popcountll(__ballot(my_tiles > 0)) * Hkv;
-      sc.whole = sched::pick_whole(launch, N, units, [&](int t) {
-        const int k = (my_tiles + t - 1) / t;   // ranges per unit
-        const int kincl = wave_scan(k);
-        cincl = kincl * t;
-        return __builtin_amdgcn_readlane(kincl, 63);
-      });
+      sc.whole = sched::pick_whole(
+          launch, N, units,
+          [&](int t) {
+            const int kincl = wave_scan((my_tiles + t - 1) / t);   // ranges per unit
+            cincl = kincl * t;
+            return __builtin_amdgcn_readlane(kincl, 63);
+          },
+          [&](int t) { return wave_most(sched::range_excess(launch, my_tiles, my_s, t)); },
+          [&]() { return __builtin_amdgcn_readlane(wave_scan(my_cost), 63); });
       if (sc.whole) my_cost = sched::unit_cost(launch, my_tiles, my_s, sc.whole);
     }
     if (!sc.whole) cincl = wave_scan(my_cost);

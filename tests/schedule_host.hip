@@ -1,5 +1,6 @@
 // The tile schedule's arithmetic on the host: what a launch's workgroups work
 // out, with plain loops in place of the wave's scans and searches.
+#include <algorithm>
 #include <vector>
 
 #include "schedule.h"
@@ -27,11 +28,23 @@ extern "C" void host_schedule(int g, int Hkv, int C_max, int P, int flat, int ti
   sc.whole = 0;
   const int N = pref[B] * Hkv;
   if (B <= 64 && !flat)
-    sc.whole = pick_whole(p, N, with_tiles * Hkv, [&](int t) {
-      int k = 0;
-      for (int b = 0; b < B; ++b) k += (seq_tiles(seqs[b], tile_keys) + t - 1) / t;
-      return k;
-    });
+    sc.whole = pick_whole(
+        p, N, with_tiles * Hkv,
+        [&](int t) {
+          int k = 0;
+          for (int b = 0; b < B; ++b) k += (seq_tiles(seqs[b], tile_keys) + t - 1) / t;
+          return k;
+        },
+        [&](int t) {
+          int e = 0;
+          for (int b = 0; b < B; ++b) e = std::max(e, range_excess(p, seq_tiles(seqs[b], tile_keys), seqs[b], t));
+          return e;
+        },
+        [&]() {
+          int c = 0;
+          for (int b = 0; b < B; ++b) c += unit_cost(p, seq_tiles(seqs[b], tile_keys), seqs[b], 0);
+          return c;
+        });
   for (int b = 0; b < B; ++b)
     cpref[b + 1] = cpref[b] + unit_cost(p, seq_tiles(seqs[b], tile_keys), seqs[b], sc.whole);
   sc.cut(p, N, cpref[B]);

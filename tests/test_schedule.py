@@ -73,6 +73,12 @@ def check(host, g, Hkv, C_max, P, flat, tile, ctx, chunk):
             assert ql == bisect.bisect_right(starts, unit + n[bb] - 1) - 1
         if whole:
             assert (b, kvh) == (bl, kvl) and g1 - g0 <= whole
+    if whole > 4:
+        # no range costs over 3.5 of its tiles more than the average one
+        w = [10 + -(-int(c) * g // 16) for c in chunk]
+        E = [12 if int(c) * g <= 32 else 9 for c in chunk]
+        mean = sum(Hkv * (a * x + e) for a, x, e in zip(n, w, E) if a) / Pe
+        assert max((min(a, whole) - 3.5) * x + e for a, x, e in zip(n, w, E) if a) <= mean
     return whole
 
 
@@ -115,3 +121,14 @@ def test_counts_tiles_only_past_31_bits(host):
         unit = tiles * (10 + -(-C_max * g // 16)) + 12
         for B in (1, 64, 500, 1024):
             assert host.host_counts_tiles(g, Hkv, C_max, B, tiles) == int(B * Hkv * unit >= 1 << 31)
+
+
+@pytest.mark.parametrize("Hkv,g,C,tile,ctx,chunk,even", [
+    (8, 4, 5, 128, [3800] * 12, [5] * 12, True),       # 192 equal ranges
+    (8, 4, 5, 128, [300] * 16, [5] * 16, True),        # whole units
+    (4, 7, 16, 128, [3800] * 24, [16] + [1] * 23, False),                        # rows differ
+    (2, 4, 4, 64, [3000 - 50 * i for i in range(56)], [4] * 56, False),          # lengths differ
+])
+def test_uneven_ranges_fall_back_to_equal_cost(host, Hkv, g, C, tile, ctx, chunk, even):
+    whole = check(host, g, Hkv, C, 256, 0, tile, ctx, chunk)
+    assert (whole > 0) == even
