@@ -92,16 +92,18 @@ SCHED_FN int unit_cost(const Launch& p, int n, uint32_t s, int whole) {
 //
 // Ranges of a fixed number of tiles are uneven where units differ in rows or
 // leave short last ranges, and the launch ends with the longest.  Where that
-// one costs over kWholeUneven half tiles more than the average range, cost is
-// cut equally after all (4 KV heads of 7 query heads, chunks of 1-16, B = 28
-// with 1-10k tokens: 74.9 us in ranges of 21 tiles, 67.8 at equal cost; 2 KV
-// heads, fp32, B = 56 with 128-3000: 53.7 and 48.5).  Fewer ranges than
-// workgroups, if even, stream as fast: 8 KV heads, B = 12 with 3800 tokens,
-// 192 ranges of 15 tiles 39.1 us, at equal cost 41.0.  Over 500 launches timed
-// both ways, the form chosen takes 0.4% longer than the better one of each with
-// 6 or 7 half tiles, 0.8% with 4, 0.5% with 8 and 0.8% without a limit.  Not
-// asked of ranges of up to kWholeShort tiles: such launches would notice the
-// two reductions (0.1 us), and none of the 500 is uneven enough.
+// one costs over kWholeUneven half tiles more than the average range (a
+// quarter of it taken over all workgroups, idle ones too), cost is cut equally
+// after all: 4 KV heads of 7 query heads, chunks of 1-16, B = 28 with 1-10k
+// tokens 74.9 us in ranges of 21 tiles, 67.8 at equal cost; B = 24 with 3800,
+// 192 ranges of 15 tiles, 56.9 and 54.2; 2 KV heads, fp32, B = 56 with
+// 128-3000 53.7 and 48.5.  Even ranges on fewer workgroups stream as fast: 8
+// KV heads, B = 12 with 3800 tokens, 192 ranges of 15 tiles, 39.1 us, at equal
+// cost 41.0.  Over 500 launches timed both ways, the form chosen takes 0.5%
+// longer than the better one of each with 6 to 8 half tiles, 0.8% with 4 and
+// 0.8% without a limit.  Not asked of ranges of up to kWholeShort tiles: such
+// launches would notice the two reductions (0.1 us), and none of the 500 is
+// uneven enough.
 //
 // N tiles and `units` units in all.  ranges(t): ranges of t tiles per KV head;
 // excess(t): the most, over the sequences, of range_excess; cost(): of one KV
@@ -121,7 +123,8 @@ SCHED_FN int pick_whole(const Launch& p, int N, int units, RANGES ranges, EXCESS
   for (int tries = 0; tries < kWholeTries; ++tries, ++t) {
     const int k = ranges(t);
     if (k * p.Hkv <= p.P) {
-      if (__builtin_expect(t > kWholeShort, 0) && (int64_t)excess(t) * k > 2 * (int64_t)cost()) return 0;
+      if (__builtin_expect(t > kWholeShort, 0) && 2 * (int64_t)excess(t) * k * p.P > (int64_t)cost() * (3 * p.P + k * p.Hkv))
+        return 0;
       return t;
     }
   }

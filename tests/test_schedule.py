@@ -74,6 +74,36 @@ def check(host, g, Hkv, C_max, P, flat, tile, ctx, chunk):
         if whole:
             assert (b, kvh) == (bl, kvl) and g1 - g0 <= whole
     if whole > 4:
+        # no range costs over 3.5 of its tiles more than the average one, which
+        # counts for three quarters, and the average over all workgroups
+        w = [10 + -(-int(c) * g // 16) for c in chunk]
+        E = [12 if int(c) * g <= 32 else 9 for c in chunk]
+        total = sum(Hkv * (a * x + e) for a, x, e in zip(n, w, E) if a)
+        most = max((min(a, whole) - 3.5) * x + e for a, x, e in zip(n, w, E) if a)
+        assert most <= 0.75 * total / Pe + 0.25 * total / P + 1e-6
+    return whole
+    assert 1 <= Pe <= P and head[3] * Pe + head[4] == Wt and 0 <= head[4] < Pe
+    bound = [q * head[3] + min(q, head[4]) for q in range(Pe + 1)]
+
+    def place(t):      # sequence, KV head and index of tile t, and its start cost
+        b = bisect.bisect_right(t0, t) - 1
+        kvh, j = divmod(t - t0[b], n[b])
+        return b, kvh, j, c0[b] + kvh * U[b] + (S[b] + j * w[b] if j else 0)
+
+    rows = rows[:Pe].tolist()
+    starts = [r[0] for r in rows]
+    assert starts[0] == 0 and rows[-1][1] == N
+    for q, (g0, g1, b, kvh, j, bl, kvl, qf0, ql0, qf1, ql1) in enumerate(rows):
+        assert g0 < g1 and (q + 1 == Pe or g1 == rows[q + 1][0])
+        assert place(g0)[:3] == (b, kvh, j) and place(g1 - 1)[:2] == (bl, kvl)
+        assert bound[q] <= place(g0)[3] and place(g1 - 1)[3] < bound[q + 1]
+        for bb, kk, qf, ql in ((b, kvh, qf0, ql0), (bl, kvl, qf1, ql1)):
+            unit = t0[bb] + kk * n[bb]
+            assert qf == bisect.bisect_right(starts, unit) - 1
+            assert ql == bisect.bisect_right(starts, unit + n[bb] - 1) - 1
+        if whole:
+            assert (b, kvh) == (bl, kvl) and g1 - g0 <= whole
+    if whole > 4:
         # no range costs over 3.5 of its tiles more than the average one
         w = [10 + -(-int(c) * g // 16) for c in chunk]
         E = [12 if int(c) * g <= 32 else 9 for c in chunk]
