@@ -38,6 +38,7 @@ HBM_PEAK_GBS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0   # dense bf16 / f16 matrix-core peak of an MI355X
 MAIN_KERNEL = "verify_attn_kernel"
 KERNEL_SOURCE = os.path.join(ROOT, "paper_2508_21706_amd", "csrc", "verify_attn.hip")
+SCHEDULE_SOURCE = os.path.join(ROOT, "paper_2508_21706_amd", "csrc", "schedule.h")
 ACCEPT_METRIC = "acceptance step: logits HBM GB/s and accepted-token decisions per second"
 ACCEPT_KERNEL = "accept_kernel"
 ACCEPT_SOURCE = os.path.join(ROOT, "paper_2508_21706_amd", "csrc", "accept.hip")
@@ -48,8 +49,12 @@ def log(msg):
 
 
 def source_digest(path: str = KERNEL_SOURCE) -> str:
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    """Of a kernel's source; of the attention kernel's with its schedule."""
+    digest = hashlib.sha256()
+    for part in (path, SCHEDULE_SOURCE) if path == KERNEL_SOURCE else (path,):
+        with open(part, "rb") as f:
+            digest.update(f.read())
+    return digest.hexdigest()[:16]
 
 
 def load_traffic(workload: str, kernel: str = MAIN_KERNEL, source: str = KERNEL_SOURCE):

@@ -105,10 +105,11 @@ typedef struct specmoe_verify_desc {
  *
  * Work split: the keys of every (sequence, KV head) are cut into tiles, and
  * the tiles of all of them are divided into at most `grid_blocks` contiguous
- * ranges of equal cost, one per persistent workgroup; a tile's cost grows
- * with the query rows (c_b * Hq / Hkv) that compute on it, so with equal
- * chunk lengths every range holds the same number of tiles (give or take
- * one).  A (sequence, KV head) whose tiles
+ * ranges, one per persistent workgroup: ranges of equal cost, in which a
+ * tile costs more the more query rows (c_b * Hq / Hkv) compute on it and the
+ * start and end of every (sequence, KV head) are charged, or, in batches of
+ * few of them, ranges of a fixed number of tiles of one (sequence, KV head)
+ * each.  A (sequence, KV head) whose tiles
  * span several ranges is computed in pieces that are merged with log-sum-exp
  * weights -- the sequence-dimension KV partition of Section 5.2 -- through
  * the workspace.  The split depends only on the lengths and grid_blocks, and
@@ -128,6 +129,9 @@ typedef struct specmoe_verify_desc {
  *   out        float32 [B, C_max, Hq, D]: attention output.
  *   lse        float32 [B, C_max, Hq]: natural-log log-sum-exp of the scaled,
  *              masked scores of each row.
+ *              (Infinities and NaN in a sequence's valid inputs can reach
+ *              all its rows of the same KV head, also rows that do not see
+ *              them, and no others.)
  *   stream     hipStream_t the work is enqueued on (NULL: the null stream).
  *   desc       host pointer to the problem description.
  * Padding rows (c_b <= i < C_max) get out = 0 and lse = -inf.  A sequence with

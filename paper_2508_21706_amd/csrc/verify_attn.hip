@@ -15,15 +15,16 @@
 //   * Key tiles: a unit's keys [0, T_b) are cut into tiles of 32 KB of K rows
 //     anchored at T_b (tile n-1 = [T_b - kTileKeys, T_b)), so the chunk's own
 //     keys sit at the end of the unit's last tile.
-//   * Stream-K schedule: the tiles of all units, in unit order, form one list
-//     cut into contiguous ranges of equal cost, one per workgroup.  A tile's
-//     cost grows with its unit's row count (a unit with many rows computes
-//     longer on a tile than the tile takes to stream); when every unit has
-//     the same rows, every workgroup streams the same number of K/V bytes.
-//     The first tile of every workgroup is located by a search of per-sequence
-//     prefix sums in LDS, computed by one wave of each workgroup from the
-//     length arrays while the others wait at a single barrier, so no host
-//     pass or second launch is needed.  A unit cut by a range
+//   * Stream-K schedule (schedule.h): the tiles of all units, in unit order,
+//     form one list cut into contiguous ranges, one per workgroup: ranges of
+//     equal cost, a tile's cost growing with its unit's row count (a unit with
+//     many rows computes longer on a tile than the tile takes to stream) and
+//     unit starts and ends charged, or, in launches of few units, ranges of a
+//     fixed number of tiles inside units.  One wave of each workgroup works
+//     out its range from the length arrays while the others wait at a single
+//     barrier, so no host pass or second launch is needed: prefix sums over
+//     the sequences, in its registers (with more than 64 sequences also in
+//     LDS), and a search among them.  A unit cut by a range
 //     boundary is a sequence-wise KV partition whose partial results must be
 //     combined, as the paper notes for its sequence-dimension KV split
 //     (Section 5.2).  Ranges are streamed in order.  The piece of a range's
@@ -176,12 +177,13 @@ struct Cfg {
   static constexpr int kQJ = kChunks / 4;                   // 16-byte Q chunks per lane
   static_assert(kTileKeys % 64 == 0, "whole 64-slot DMA instructions");
   // LDS beside the stages: packed lengths and tile prefix sums of up to
-  // kMaxSeqs sequences, the key-split merge statistics and the hand-off words
-  static constexpr int kLdsFixed = kMaxSeqs * 4 + (kMaxSeqs + 1) * 4 + kConsumers * 2 * kBlk * 4 + 512;
+  // kMaxSeqs sequences, the key-split merge statistics and the schedule's and
+  // hand-off words
+  static constexpr int kLdsFixed = 2 * kMaxSeqs * 4 + kConsumers * 2 * kBlk * 4 + 512;
   // the rest of the 160 KB: the cost prefix sums while the schedule is made,
-  // then the piece of the range's first segment until the range's last tile
+  // then the piece of the range's first segment until it is published
   static constexpr int kPieceLds = (160 * 1024 - kStages * kStage - kLdsFixed) / 16 * 16;
-  static_assert(kPieceLds >= (kMaxSeqs + 1) * 4, "LDS budget");
+  static_assert(kPieceLds >= kMaxSeqs * 4, "LDS budget");
   // the key slots of a unit of one row block, and the scratch of their merge
   // (whole states) and of that of two slots (half states of every wave)
   static constexpr int kMaxSlots = kConsumers < kNKB / 2 ? kConsumers : kNKB / 2;
@@ -479,12 +481,13 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
   using C = Cfg<W16, D>;
   __shared__ __attribute__((aligned(16))) char smem[kStages * C::kStage];
   __shared__ uint32_t seqs[kMaxSeqs];     // packed (T, c) of every sequence of the launch
-  __shared__ int pref[kMaxSeqs + 1];      // tiles per KV head of the sequences before b
-  // the cost of one KV head's tiles of the sequences before b; with HOLD it
-  // shares its LDS with the held piece (O rows, then the rows' max and sum),
-  // which is written only once the schedule has been made
+  // (more than 64 sequences) the tiles and the cost of one KV head's units of
+  // the sequences before b; with HOLD the cost shares its LDS with the held
+  // piece (O rows, then the rows' max and sum), which is written only once the
+  // schedule has been made
+  __shared__ int pref[kMaxSeqs];
   __shared__ __attribute__((aligned(16))) char piece_lds[HOLD ? C::kPieceLds : 16];
-  __shared__ int cpref_own[HOLD ? 1 : kMaxSeqs + 1];
+  __shared__ int cpref_own[HOLD ? 1 : kMaxSeqs];
   int* const cpref = HOLD ? reinterpret_cast<int*>(piece_lds) : cpref_own;
   __shared__ float mst[kConsumers][2][kBlk];   // key-split merge: max and sum of each wave's rows
   __shared__ int sh_flag[2];              // "this piece completed its unit", for the two pieces
@@ -1047,8 +1050,8 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
     }
     pend = false;
     if (HOLD && pub0.state == 3 && v == pub0.v) {
-      // the held piece (the first segment's, slot 2 pid) goes out now, while
-      // the range's last tile streams in; it is counted two iterations later
+      // the held piece (the first segment's, slot 2 pid) goes out now, three
+      // quarters into the range; it is counted two iterations later
       cbar();   // every wave has written its slice of it
       const __amdgpu_buffer_rsrc_t ws_o_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_o, 0, p.ws_o_bytes, kBufferFormat);
       const __amdgpu_buffer_rsrc_t ws_lse_rsrc =
@@ -1309,14 +1312,9 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
       const int d_lo = kslot * s_db;   // the first of this wave's d blocks
       const int unit_first = gt - j;                 // global index of the unit's tile 0
       const bool whole = seg_g == unit_first && j == n - 1;
-      // The piece of the range's first segment is held in LDS and stored
-      // only at the range's last tile, when it fits there and more tiles
-      // follow: stores issued while the range's tiles stream in slow the rest
-      // of the stream down, stores late in it much less.  It is written by
-      // the key-split merge below (units of one or two row blocks), not yet
-      // normalised: O rows, then (max, sum) per row.  (Those units' waves
-      // pass consumer barriers at each unit end, so by then the cost sums
-      // that share the LDS are no longer read.)
+      // The piece of the range's first segment is held in LDS until three
+      // quarters into the range, when it fits there and more tiles follow.
+      // (Where the cost prefix sums were, which only the schedule reads.)
       const bool hold =
           HOLD && !whole && seg_g == g0 && v + 1 < count && nks > 1 && R * (D + 2) * 4 <= C::kPieceLds;
       // Merge of NKS key slots; the result is left in o[0 .. s_db - 1].  Of two
@@ -1430,12 +1428,8 @@ __global__ __launch_bounds__(kThreads, 1) void verify_attn_kernel(Params p) {
         q.unit = b * Hkv + kvh;
         q.v = v + 1;   // the iteration that stores it
         q.rows = R;
-        // The piece of the range's first segment is held in LDS and stored
-        // only at the range's last tile, when it fits there and more tiles
-        // follow: stores issued while the range's tiles stream in slow the
-        // rest of the stream down (measured), stores late in it much less.
-        // (Units with one or two row blocks: their waves pass consumer
-        // barriers at each unit end, so the cost sums are no longer read.)
+        // Stores issued while the range's tiles stream in slow the rest of
+        // the stream down (measured), stores late in it much less.
         if (hold) {
           pend_ok = false;   // written to LDS by the key-split merge above
           q.state = 3;
